@@ -161,6 +161,8 @@ Layout make_layout(const moa_engine_cfg& c) {
   // split-K partials: a prefill-sized step unsplit, or a full decode batch
   // split up to 8 ways (a few hundred rows need the split to fill the CUs)
   int64_t pc = std::max(L.Tmax, (int64_t)8 * c.max_num_seqs) * std::max(qkv, d);
+  // fp32 gate-up once wrote its sums here; an engine's allocation-free steps
+  // are still refused at the same sizes
   if (c.dtype == MOA_F32) pc = std::max(pc, L.Tmax * 2 * F);
   L.part_cap = pc;
   L.token_store = c.token_store ? c.token_store : (int64_t)64 << 20;
@@ -1237,11 +1239,10 @@ moa_status enqueue_step(moa_engine* e, const std::vector<int64_t>& admitted, int
           gemm_cost(ga, EPI_SWIGLU, gb, gf);
           LAUNCH_GEMM(MOA_K_GEMM_GATEUP, lg, gb, gf, launch_gemm(st, bf, ga, EPI_SWIGLU, mt, nt), "gate-up gemm");
         } else {
-          plan_gemm(e, weights([l](const ModelDev& x) { return x.wgu[l]; }), b.g0, b.ng, d, 2 * F, EPI_F32, e->xn, 0,
-                    b.part, nullptr, 0, false, ga, mt, nt, lg);
-          gemm_cost(ga, EPI_F32, gb, gf);
-          LAUNCH_GEMM(MOA_K_GEMM_GATEUP, lg, gb, gf, launch_gemm(st, bf, ga, EPI_F32, mt, nt), "gate-up gemm");
-          HIPCHK(launch_swiglu_f32(st, b.part + ro * 2 * F, (float*)e->h + ro * F, b.nr, F), "swiglu");
+          plan_gemm(e, weights([l](const ModelDev& x) { return x.wgu[l]; }), b.g0, b.ng, d, 2 * F, EPI_SWIGLU, e->xn, 0,
+                    (float*)e->h, nullptr, 0, false, ga, mt, nt, lg);
+          gemm_cost(ga, EPI_SWIGLU, gb, gf);
+          LAUNCH_GEMM(MOA_K_GEMM_GATEUP, lg, gb, gf, launch_gemm(st, bf, ga, EPI_SWIGLU, mt, nt), "gate-up gemm");
         }
         plan_gemm(e, weights([l](const ModelDev& x) { return x.wdown[l]; }), b.g0, b.ng, F, d, EPI_F32, e->h, h_lo,
                   b.part, nullptr, 0, true, ga, mt, nt, lg);

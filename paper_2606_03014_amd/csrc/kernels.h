@@ -36,7 +36,7 @@ struct GemmArgs {
   int ksteps;          // 32-wide k steps per split
   float* out;          // f32 output / partials: out + s*out_split + row*N + n
   size_t out_split;
-  uint16_t* hout;      // SwiGLU epilogue output, split bf16 [rows][N/2] (hi), lo plane at +h_lo
+  uint16_t* hout;      // bf16 SwiGLU epilogue output, split bf16 [rows][N/2] (hi), lo plane at +h_lo (f32: out, [rows][N/2])
   size_t h_lo;
 };
 
@@ -90,8 +90,6 @@ hipError_t launch_add_rmsnorm(hipStream_t st, bool bf16, float* x, const float* 
                               ModelPtrs gamma, void* out, size_t out_lo, int d, float eps);
 
 hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, int mt, int nt);
-
-hipError_t launch_swiglu_f32(hipStream_t st, const float* gu, float* h, int T, int ffn);
 
 hipError_t launch_rope_kv(hipStream_t st, bool bf16, const float* part, int nsplit, size_t split_stride,
                           const int* row_pos, const int* row_bt, const int* bt_store,

@@ -677,10 +677,26 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs a, int nwg) {
 }
 
 // ------------------------------------------------------------ fp32 GEMM
-// Plain fp32 FMA GEMM for the fp32 engine mode: a workgroup computes 16 rows
-// x 64 columns; W is row-major [N][K].
+// The fp32 engine mode: Y = X . W^T on the fp32 MFMA (16x16x4, exact fp32
+// products), W row-major [N][K]. Small models' fp32 steps are bound by latency
+// (their weights fit the caches), so the work of a launch is spread wide and
+// every lane keeps 16-byte loads in flight:
+//  * a workgroup owns 16 rows x CT 16-column tiles, its four waves a quarter
+//    of K each; their sums meet in LDS in fixed order;
+//  * lane l loads 4 consecutive k of row (A) or column (B) l % 16 at
+//    k = 16 j + 4 (l / 16): element i of that quad feeds the i-th of four
+//    MFMAs, which permutes k the same way in A and B and changes no product.
+// K is a multiple of 64 (d_model, n_heads * head_dim and ffn_dim all are).
+// EPI_SWIGLU (gate-up, rows of W are [gate(F) | up(F)]): tiles 2p and 2p + 1 are
+// the gate and up columns of the same 16 hidden units, and h = silu(gate) * up
+// is written by the same launch.
+// Before: one lane per column walking K alone, 4 rows per lane: 62.8 us per
+// launch over the tiny fp32 mixture's passes (d 256, ffn 1024, 1-32 rows).
+template <int CT, int EPI>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs a) {
-  const int item = blockIdx.x;
+  constexpr int SUB = 4 / CT;                        // workgroups per 64-column item
+  __shared__ float red[4][CT][256];
+  const int item = blockIdx.x / SUB, sub = blockIdx.x % SUB;
   const void* Wg = a.g[0].W;
   int row0 = a.g[0].row0, nrows = a.g[0].nrows, n_mc = a.g[0].n_mc, item0 = a.g[0].item0;
 #pragma unroll
@@ -691,33 +707,49 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs a) {
   }
   const int idx = item - item0;
   const int mc = idx % n_mc, nb = idx / n_mc;
-  const int colw = nb * 64 + (threadIdx.x & 63);
-  const int rb = row0 + mc * 16 + (threadIdx.x >> 6) * 4;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int tile0 = nb * 4 + sub * CT;               // first 16-column tile (SWIGLU: unit tile tile0 / 2)
+  const int half = a.N >> 1;
+  const int rbase = row0 + mc * 16;
   const int rend = row0 + nrows;
-  const float* W = (const float*)Wg + (size_t)colw * a.K;
-  const float* X = (const float*)a.X;
-  const float* xr[4];
+  auto col0 = [&](int c) { return EPI == EPI_SWIGLU ? (tile0 / 2 + c / 2) * 16 + (c & 1) * half : (tile0 + c) * 16; };
+  const int kq = a.K >> 2;
+  const size_t ko = (size_t)w * kq + 4 * (lane >> 4);
+  const float* xp = (const float*)a.X + (size_t)min(rbase + (lane & 15), rend - 1) * a.K + ko;
+  const float* wp[CT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) xr[i] = X + (size_t)min(rb + i, rend - 1) * a.K;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < a.K; ++k) {
-    const float w = W[k];
+  for (int c = 0; c < CT; ++c) wp[c] = (const float*)Wg + (size_t)(col0(c) + (lane & 15)) * a.K + ko;
+  f32x4_t acc[CT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = fmaf(xr[i][k], w, acc[i]);
+  for (int c = 0; c < CT; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int k = 0; k < kq; k += 16) {
+    const f32x4_t x = *(const f32x4_t*)(xp + k);
+    f32x4_t b[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) b[c] = *(const f32x4_t*)(wp[c] + k);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], b[c][i], acc[c], 0, 0, 0);
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (rb + i < rend) a.out[(size_t)(rb + i) * a.N + colw] = acc[i];
-}
-
-// h = silu(gate) * up for the fp32 mode; gu rows are [gate(ffn) | up(ffn)].
-__global__ __launch_bounds__(256) void k_swiglu_f32(const float* __restrict__ gu, float* __restrict__ h,
-                                                    int ffn) {
-  const int t = blockIdx.x;
-  const float* r = gu + (size_t)t * 2 * ffn;
-  for (int i = threadIdx.x; i < ffn; i += 256) {
-    const float g = r[i];
-    h[(size_t)t * ffn + i] = g / (1.f + expf(-g)) * r[ffn + i];
+  for (int c = 0; c < CT; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[w][c][(4 * (lane >> 4) + i) * 16 + (lane & 15)] = acc[c][i];
+  __syncthreads();
+  const int row = rbase + (threadIdx.x >> 4), cc = threadIdx.x & 15;
+  if (row >= rend) return;
+  float y[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c)
+    y[c] = (red[0][c][threadIdx.x] + red[1][c][threadIdx.x]) + (red[2][c][threadIdx.x] + red[3][c][threadIdx.x]);
+  if (EPI == EPI_F32) {
+#pragma unroll
+    for (int c = 0; c < CT; ++c) a.out[(size_t)row * a.N + col0(c) + cc] = y[c];
+  } else {
+#pragma unroll
+    for (int c = 0; c + 1 < CT; c += 2) a.out[(size_t)row * half + col0(c) + cc] = y[c] / (1.f + expf(-y[c])) * y[c + 1];
   }
 }
 
@@ -1450,16 +1482,21 @@ hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, in
     return hipGetLastError();
   }
   if (!bf16) {
-    klaunch(k_gemm_f32, dim3(a.total_items), dim3(256), st, a);
+    if (a.K % 64 != 0 || a.N % 64 != 0) return hipErrorInvalidValue;
+    // four column tiles per workgroup once that fills the chip four times over
+    // (it reads each activation row a quarter as often), else one (SwiGLU: two)
+    const bool wide = a.total_items >= 1024;
+    const dim3 b(256);
+    if (epi == EPI_SWIGLU) {
+      if (wide) klaunch(k_gemm_f32<4, EPI_SWIGLU>, dim3(a.total_items), b, st, a);
+      else klaunch(k_gemm_f32<2, EPI_SWIGLU>, dim3(2 * a.total_items), b, st, a);
+    } else {
+      if (wide) klaunch(k_gemm_f32<4, EPI_F32>, dim3(a.total_items), b, st, a);
+      else klaunch(k_gemm_f32<1, EPI_F32>, dim3(4 * a.total_items), b, st, a);
+    }
     return hipGetLastError();
   }
   return hipErrorInvalidValue;                        // no bf16 kernel for this tile code
-}
-
-hipError_t launch_swiglu_f32(hipStream_t st, const float* gu, float* h, int T, int ffn) {
-  if (T <= 0) return hipSuccess;
-  klaunch(k_swiglu_f32, dim3(T), dim3(256), st, gu, h, ffn);
-  return hipGetLastError();
 }
 
 hipError_t launch_rope_kv(hipStream_t st, bool bf16, const float* part, int nsplit, size_t split_stride,
