@@ -167,7 +167,7 @@ Layout make_layout(const moa_engine_cfg& c) {
   L.part_cap = pc;
   L.token_store = c.token_store ? c.token_store : (int64_t)64 << 20;
   L.block_store = c.block_store ? c.block_store : (int64_t)16 << 20;
-  L.meta_ints = 4 * L.Tmax + 2 * L.Rmax + 8 * L.items_cap + 4 * L.red_cap + 4 * L.Tmax;
+  L.meta_ints = 4 * L.Tmax + 2 * L.Rmax + 8 * L.items_cap + 4 * L.red_cap + 4 * L.Tmax + 4 * L.Rmax;
   L.block_bytes = (size_t)Lr * nkv * 2 * kBlock * hd * L.esz;
   L.kv_bytes = L.block_bytes * (size_t)c.num_kv_blocks;
   const size_t per_layer = (size_t)(2 * d + qkv * d + d * nh * hd + 3 * F * d) * L.esz;
@@ -921,22 +921,22 @@ namespace {
 // Write the injected K/V history of admitted requests into their blocks.
 // With caller data: stage it through the logits buffer (idle between steps;
 // the stream is drained first) one (layer, K|V) position range at a time and
-// scatter it with a kernel. Without: fill on the device from a hash of
-// (request, layer, K|V, position, head, dim).
-moa_status write_histories(moa_engine* e, const std::vector<int64_t>& admitted) {
+// scatter it with a kernel. Without: one launch fills all of them on the device
+// from a hash of (request, layer, K|V, position, head, dim); `fills` lists them
+// (nitems KV blocks in all) and lies at dev_fills once the step's metadata is up.
+moa_status write_histories(moa_engine* e, const std::vector<int64_t>& admitted, const FillReq* dev_fills, int nfills,
+                           int nitems) {
   const moa_model_cfg& g = e->cfg.model;
   const size_t esz = e->lay.esz;
   const size_t row = (size_t)g.n_kv_heads * g.head_dim;             // elements per position
   const size_t cap_rows = std::max<size_t>(1, (size_t)e->lay.Rmax * g.vocab * 4 / (row * esz));
   bool drained = false;
+  if (nfills > 0)
+    HIPCHK(launch_kv_fill(e->stream, e->bf16, e->kv, e->bt_store, dev_fills, nfills, nitems, g.n_layers,
+                          e->cfg.num_kv_blocks, g.n_kv_heads, g.head_dim), "history fill");
   for (int64_t id : admitted) {
     Request& r = e->reqs[id];
-    if (!r.history || r.shift == 0) continue;
-    if (r.host_kv.empty()) {
-      HIPCHK(launch_kv_fill(e->stream, e->bf16, e->kv, e->bt_store + r.bt_off, r.shift, g.n_layers,
-                            e->cfg.num_kv_blocks, g.n_kv_heads, g.head_dim, (uint32_t)r.id), "history fill");
-      continue;
-    }
+    if (!r.history || r.shift == 0 || r.host_kv.empty()) continue;
     if (!drained) {
       HIPCHK(hipStreamSynchronize(e->stream), "history sync");
       drained = true;
@@ -1016,20 +1016,38 @@ moa_status enqueue_step(moa_engine* e, const std::vector<int64_t>& admitted, int
     pml = (float*)(sc + pb * e->nstreams + align_up((size_t)L.slots_cap * g.n_heads * g.head_dim * 4, 256));
   }
 
-  // ---- stage: metadata, then prompts and block lists of admitted requests
-  // (an allocation-free step stages only the metadata, in the slot sized for
-  // it at moa_create, and uploads prompts and block lists from host copies)
+  // ---- stage: metadata, then prompts and block lists of admitted requests,
+  // then the table of runs that one launch copies from there to the device.
+  // (An allocation-free step never grows the staging slot moa_create sized for
+  // the metadata: prompts and block lists that do not fit beside it go up from
+  // host copies, one copy each.)
   const int nitems = (int)e->items.size(), nred = (int)e->red.size(), npre = (int)e->pitems.size();
-  size_t meta_ints = 4 * (size_t)T + 2 * (size_t)R + 8 * (size_t)nitems + 4 * (size_t)nred + 4 * (size_t)npre;
-  size_t up_ints = 0;
-  if (!noalloc)
-    for (int64_t id : admitted) up_ints += e->reqs[id].prompt.size() + e->reqs[id].blocks.size();
+  std::vector<FillReq> fills;
+  int fill_items = 0;
+  size_t up_ints = 0, up_runs = 0;
+  auto runs_of = [](size_t n) { return (n + kCopyInts - 1) / kCopyInts; };
+  for (int64_t id : admitted) {
+    const Request& r = e->reqs[id];
+    up_ints += r.prompt.size() + r.blocks.size();
+    up_runs += runs_of(r.prompt.size()) + runs_of(r.blocks.size());
+    if (r.history && r.shift > 0 && r.host_kv.empty()) {
+      fills.push_back({fill_items, (int)r.bt_off, r.shift, (uint32_t)r.id});
+      fill_items += (r.shift + kBlock - 1) / kBlock;
+    }
+  }
+  const size_t meta_ints = 4 * (size_t)T + 2 * (size_t)R + 8 * (size_t)nitems + 4 * (size_t)nred +
+                           4 * (size_t)npre + 4 * fills.size();
+  const size_t meta_runs = runs_of(meta_ints);
+  // the table starts on a 16-byte boundary
+  auto stage_ints = [&](size_t payload, size_t runs) { return align_up(payload, 4) + 4 * runs; };
+  bool staged = true;
+  if (noalloc && e->stage[slot].cap < stage_ints(meta_ints + up_ints, meta_runs + up_runs) * 4) staged = false;
   if (noalloc && e->stage[slot].cap < meta_ints * 4) return hip_fail(e, hipErrorOutOfMemory, "staging size");
-  st = ensure_stage(e, slot, (meta_ints + up_ints) * 4);
+  st = ensure_stage(e, slot, staged ? stage_ints(meta_ints + up_ints, meta_runs + up_runs) * 4 : meta_ints * 4);
   if (st != MOA_OK) return st;
   int* hb = (int*)e->stage[slot].buf;
   size_t o = 0;
-  auto put = [&](const void* p, size_t n_int) { std::memcpy(hb + o, p, n_int * 4); o += n_int; };
+  auto put = [&](const void* p, size_t n_int) { if (n_int) std::memcpy(hb + o, p, n_int * 4); o += n_int; };
   const size_t o_tok = o; put(e->r_tok.data(), T);
   const size_t o_pos = o; put(e->r_pos.data(), T);
   const size_t o_bt = o; put(e->r_bt.data(), T);
@@ -1039,10 +1057,28 @@ moa_status enqueue_step(moa_engine* e, const std::vector<int64_t>& admitted, int
   const size_t o_it = o; put(e->items.data(), 8 * (size_t)nitems);
   const size_t o_rd = o; put(e->red.data(), 4 * (size_t)nred);
   const size_t o_pi = o; put(e->pitems.data(), 4 * (size_t)npre);
-  HIPCHK(hipMemcpyAsync(e->meta, hb, meta_ints * 4, hipMemcpyHostToDevice, e->stream), "meta upload");
-  for (int64_t id : admitted) {
-    Request& r = e->reqs[id];
-    if (noalloc) {
+  const size_t o_fl = o; put(fills.data(), 4 * fills.size());
+  if (staged) {
+    CopyEntry* runs = (CopyEntry*)(hb + align_up(meta_ints + up_ints, 4));
+    int nruns = 0;
+    auto add = [&](size_t src, size_t n, int64_t dst, int to) {
+      for (size_t k = 0; k < n; k += kCopyInts)
+        runs[nruns++] = {(int)(src + k), (int)(dst + (int64_t)k), (int)std::min<size_t>(kCopyInts, n - k), to};
+    };
+    add(0, meta_ints, 0, 0);
+    for (int64_t id : admitted) {
+      Request& r = e->reqs[id];
+      add(o, r.prompt.size(), r.tok_off, 1);
+      put(r.prompt.data(), r.prompt.size());
+      add(o, r.blocks.size(), r.bt_off, 2);
+      put(r.blocks.data(), r.blocks.size());
+      std::vector<int32_t>().swap(r.prompt);
+    }
+    HIPCHK(launch_upload(e->stream, hb, runs, nruns, CopyBases{{e->meta, e->tok_store, e->bt_store}}), "step upload");
+  } else {
+    HIPCHK(hipMemcpyAsync(e->meta, hb, meta_ints * 4, hipMemcpyHostToDevice, e->stream), "meta upload");
+    for (int64_t id : admitted) {
+      Request& r = e->reqs[id];
       // r.blocks lives as long as the request; the prompt copy until this step completes
       HIPCHK(hipMemcpyAsync(e->tok_store + r.tok_off, r.prompt.data(), r.prompt.size() * 4, hipMemcpyHostToDevice,
                             e->stream), "prompt upload");
@@ -1050,19 +1086,9 @@ moa_status enqueue_step(moa_engine* e, const std::vector<int64_t>& admitted, int
                             e->stream), "block list upload");
       e->keepalive[slot].push_back(std::move(r.prompt));
       r.prompt = std::vector<int32_t>();
-      continue;
     }
-    const size_t a = o;
-    put(r.prompt.data(), r.prompt.size());
-    HIPCHK(hipMemcpyAsync(e->tok_store + r.tok_off, hb + a, r.prompt.size() * 4, hipMemcpyHostToDevice, e->stream),
-           "prompt upload");
-    const size_t b = o;
-    put(r.blocks.data(), r.blocks.size());
-    HIPCHK(hipMemcpyAsync(e->bt_store + r.bt_off, hb + b, r.blocks.size() * 4, hipMemcpyHostToDevice, e->stream),
-           "block list upload");
-    std::vector<int32_t>().swap(r.prompt);
   }
-  st = write_histories(e, admitted);
+  st = write_histories(e, admitted, (const FillReq*)(e->meta + o_fl), (int)fills.size(), fill_items);
   if (st != MOA_OK) return st;
   StepDev sd;
   sd.row_tok = e->meta + o_tok;
@@ -1617,20 +1643,24 @@ moa_status moa_collect(moa_engine* e, int64_t upto_step, moa_result* res, int32_
     // been reused since, that step already completed), then copy on the side stream.
     for (int i = 0; i < kStageSlots; ++i)
       if (e->ev_step[i] == last) HIPCHK(hipEventSynchronize(e->ev[i]), "collect wait");
-    if ((size_t)ntok > e->pinned_out_cap) {
+    // tokens, then the table of runs one launch copies them by
+    const size_t need = align_up((size_t)ntok, 4) + 4 * (size_t)n;
+    if (need > e->pinned_out_cap) {
       if (e->pinned_out) HIPCHK(hipHostFree(e->pinned_out), "hipHostFree");
       e->pinned_out = nullptr;
-      size_t cap2 = std::max((size_t)ntok, (size_t)1 << 16);
+      e->pinned_out_cap = 0;
+      size_t cap2 = std::max(need, (size_t)1 << 16);
       HIPCHK(hipHostMalloc((void**)&e->pinned_out, cap2 * 4, hipHostMallocDefault), "hipHostMalloc");
       e->pinned_out_cap = cap2;
     }
+    CopyEntry* runs = (CopyEntry*)(e->pinned_out + align_up((size_t)ntok, 4));
     int64_t o = 0;
     for (int32_t i = 0; i < n; ++i) {
       const Request& r = e->reqs[e->done[i]];
-      HIPCHK(hipMemcpyAsync(e->pinned_out + o, e->tok_store + r.tok_off + r.P - r.shift, (size_t)r.G * 4,
-                            hipMemcpyDeviceToHost, e->copy_stream), "collect copy");
+      runs[i] = {(int)(r.tok_off + r.P - r.shift), (int)o, r.G, 0};
       o += r.G;
     }
+    HIPCHK(launch_gather(e->copy_stream, e->tok_store, runs, n, e->pinned_out), "collect copy");
     HIPCHK(hipStreamSynchronize(e->copy_stream), "collect sync");
     std::memcpy(tok_buf, e->pinned_out, (size_t)ntok * 4);
   } else {

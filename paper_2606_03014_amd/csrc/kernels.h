@@ -116,12 +116,25 @@ hipError_t launch_attn_reduce(hipStream_t st, bool bf16, const ReduceItem* red, 
 
 // Injected history. scatter: src [n][n_kv][hd] (engine dtype) -> positions
 // [p0, p0 + n) of plane (layer, kv: 0 K / 1 V) through the request's block list.
-// fill: positions [0, ctx) of every layer from a hash of (tag, layer, kv,
-// position, head, dim), values in [-1, 1).
+// fill: for every entry of reqs, positions [0, ctx) of every layer from a hash of
+// (tag, layer, kv, position, head, dim), values in [-1, 1). Its KV blocks are
+// items [item0, item0 + ceil(ctx / 16)), item0 counting up over the entries from 0
+// to nitems; head_dim 64 or 128.
+struct FillReq { int item0, bt_off, ctx; uint32_t tag; };
 hipError_t launch_kv_scatter(hipStream_t st, bool bf16, const void* src, void* kv, const int* blocks, int p0, int n,
                              int layer, int kv_sel, int num_blocks, int n_kv, int hd);
-hipError_t launch_kv_fill(hipStream_t st, bool bf16, void* kv, const int* blocks, int ctx, int n_layers,
-                          int num_blocks, int n_kv, int hd, uint32_t tag);
+hipError_t launch_kv_fill(hipStream_t st, bool bf16, void* kv, const int* bt_store, const FillReq* reqs, int nreqs,
+                          int nitems, int n_layers, int num_blocks, int n_kv, int hd);
+
+// Move n ints per entry between pinned host memory and the device in one
+// launch (entries of more than kCopyInts are cut by the caller). upload: host +
+// src -> base[to] + dst; gather: store + src -> host + dst. The entries lie in
+// pinned host memory too.
+constexpr int kCopyInts = 1024;
+struct CopyEntry { int src, dst, n, to; };
+struct CopyBases { int* p[3]; };
+hipError_t launch_upload(hipStream_t st, const int* host, const CopyEntry* entries, int nentries, CopyBases base);
+hipError_t launch_gather(hipStream_t st, const int* store, const CopyEntry* entries, int nentries, int* host);
 
 hipError_t launch_argmax(hipStream_t st, const float* logits, int R, int V, const int* lm_dst,
                          int* tok_store);

@@ -5,8 +5,9 @@ bf16 ones against the oracle with a bf16 K/V cache, the bounds of the other GPU 
 import numpy as np
 import pytest
 
-from moa_inputs import ModelShape, generate_weights
+from moa_inputs import ModelShape, f32_to_bf16_bits, generate_weights, pack_blob
 from moa_inputs.configs import EngineConsts
+from paper_2606_03014_amd import Engine
 from tests.gpu_helpers import compare, run_requests
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +37,57 @@ def _check(shape, dtype, lens, G, seed, models=1, consts=None):
 def test_fp32_gemm_edges(ffn, vocab, lens):
     shape = ModelShape(n_layers=1, d_model=256, n_heads=1, n_kv_heads=1, head_dim=64, ffn_dim=ffn, vocab=vocab)
     _check(shape, "f32", lens, 3, seed=ffn + vocab, models=min(2, len(lens)))
+
+
+def _mix(x):
+    for shift, mul in ((16, 0x7FEB352D), (15, 0x846CA68B)):
+        x = ((x ^ (x >> np.uint64(shift))) * np.uint64(mul)) & np.uint64(0xFFFFFFFF)
+    return x ^ (x >> np.uint64(16))
+
+
+def _hash_history(shape, dtype, tag, ctx):
+    """The device-filled history as a host array [n_layers, 2, ctx, n_kv, head_dim]."""
+    u64, m32 = np.uint64, np.uint64(0xFFFFFFFF)
+    plane = np.arange(2 * shape.n_layers, dtype=u64).reshape(-1, 1, 1)
+    pos = np.arange(ctx, dtype=u64).reshape(1, -1, 1)
+    el = np.arange(shape.n_kv_heads * shape.head_dim, dtype=u64).reshape(1, 1, -1)
+    u = _mix((u64(tag * 0x9E3779B9) & m32) ^ _mix((plane << u64(24)) ^ pos) ^ ((el * u64(0x85EBCA6B)) & m32))
+    v = ((u >> u64(8)).astype(np.float32) / np.float32(8388608.0) - np.float32(1.0))
+    v = v.reshape(shape.n_layers, 2, ctx, shape.n_kv_heads, shape.head_dim)
+    return f32_to_bf16_bits(v) if dtype == "bf16" else v
+
+
+# one launch fills every admitted history (KV blocks that are whole, part and absent; several admissions in one step
+# and, with three seats, in later ones), one uploads their tokens and block lists, one gathers the tokens
+@pytest.mark.parametrize("dtype,hd", [("f32", 64), ("bf16", 64), ("f32", 128), ("bf16", 128)])
+@pytest.mark.parametrize("seats", [3, 16])
+def test_device_filled_histories_equal_uploaded_ones(dtype, hd, seats):
+    shape = ModelShape(n_layers=2, d_model=256, n_heads=4, n_kv_heads=2, head_dim=hd, ffn_dim=256, vocab=512)
+    w = generate_weights(shape, dtype, 4, 97, 0)
+    ctxs = [0, 1, 15, 16, 17, 31, 255, 256, 257, 40]
+    consts = EngineConsts(num_kv_blocks=256, max_num_seqs=seats, max_prefill_tokens=64, max_model_len=2048)
+    prompt = np.random.default_rng(8).integers(0, shape.vocab, 1500).astype(np.int32)    # past one copied run
+    got = []
+    for upload in (False, True):
+        eng = Engine(shape, dtype, consts, 1)
+        try:
+            mid = eng.load(pack_blob(w, shape))
+            caps, rids = [], []
+            for i, n in enumerate(ctxs):
+                kv = _hash_history(shape, dtype, i, n) if upload and n else None
+                rids.append(eng.submit_with_history(mid, 5 * i, n, 3, kv))
+                caps.append(np.full(3 * shape.vocab, np.nan, dtype=np.float32))
+                eng.capture_logits(rids[-1], caps[-1])
+            rids.append(eng.submit(prompt, mid, 4))
+            while eng.step().step >= 0:
+                pass
+            out = {r[0]: r[3] for r in eng.collect()}
+            eng.sync()
+            got.append(([out[r] for r in rids], caps))
+        finally:
+            eng.close()
+    for i in range(len(ctxs)):
+        assert np.all(np.isfinite(got[0][1][i]))
+        assert np.array_equal(got[0][1][i], got[1][1][i]), f"history of {ctxs[i]}: logits differ"
+    for a, b in zip(got[0][0], got[1][0]):
+        assert np.array_equal(a, b)
