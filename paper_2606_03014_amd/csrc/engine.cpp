@@ -22,7 +22,6 @@ using namespace moa;
 namespace {
 
 constexpr int kStageSlots = 4;    // steps that may be in flight (pinned staging ring)
-constexpr int kTargetWaves = 4096;
 constexpr int kBigMinRows = 256;    // a row group this large takes the large-M plan (128-row chunks)
 constexpr int kBigTargetWgs = 256;  // one workgroup per CU
 // Large-M k-split cost, fitted to cold-weight sweeps of the 8B projections
@@ -585,27 +584,30 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
       return;
     }
   }
-  const int wmt = maxM <= 16 ? 1 : (maxM <= 32 ? 2 : 4);
-  const int wnt = (maxM > 64 && N % 256 == 0) ? 4 : 2;
-  // workgroup items: 16*wmt rows x 64*wnt columns (every bf16 projection
-  // width is a multiple of 128: moa_create checks it)
+  // Small-M kernel: items of 16*wmt rows x 64*wnt columns (every bf16
+  // projection width is a multiple of 128: moa_create checks it). Up to 8 rows
+  // it packs both activation planes into one MFMA (wmt 1, wnt 2) on workgroups
+  // of 32 columns; else on workgroups of 64.
+  const int wmt = maxM <= 8 ? 1 : (maxM <= 16 && N % 256 == 0 ? 1 : (maxM <= 32 ? 2 : 4));
+  const int wnt = (wmt == 1 && maxM > 8) ? 4 : 2;
   mt = kWgTile + wmt;
   nt = wnt;
   const int tiles = N / (64 * wnt);
   const int rows_per = 16 * wmt;
-  int target = kTargetWaves / 4, base = 0;
-  for (int g = 0; g < in.ngroups; ++g) base += ((in.nrows[g] + rows_per - 1) / rows_per) * tiles;
-  // split-K granularity and target, from weight-streaming sweeps with cold
-  // weights: deep-K projections (K >= 4N) stream best with half the
-  // workgroups (longer k runs per workgroup); square ones at <= 8 rows with
-  // twice as many (k runs of 4 stages)
-  int kmul = 8;
-  if (K >= 4 * N) target /= 2;
-  else if (K == N && maxM <= 8) { target *= 2; kmul = 4; }
+  int base = 0, chunks = 0;
+  for (int g = 0; g < in.ngroups; ++g) chunks += (in.nrows[g] + rows_per - 1) / rows_per;
+  base = chunks * (N / (maxM <= 8 ? 32 : 64));       // workgroups per k-split
+  // k-split: 4, which with the waves' own split puts all of a qkv or O matrix in
+  // flight at once; 2 for a long K (from 12,288: a wave still has 48 k-steps),
+  // 8 where 4 leaves CUs idle. At least 4 k-steps per wave up to 8 rows, 2 above.
+  // Swept at 1, 8, 16, 32 and 64 rows on one and three models of both widths:
+  // within 5% of the best power of two but for 8B qkv at 16 rows (12.9 us, 11.6 at 8).
   int S = 1;
   if (allow_split) {
-    while (base * S < target && KS % (S * 2 * kmul) == 0 &&
-           (int64_t)S * 2 * totalM * N <= e->lay.part_cap && S < 16)
+    int want = maxM <= 8 ? (KS >= 384 ? 2 : 4) : (base * 4 < 256 ? 8 : 4);
+    const int min_k = maxM <= 8 ? 4 : 2;
+    while (S < want && KS % (S * 2 * 4) == 0 && KS / (S * 2 * 4) >= min_k &&
+           (int64_t)S * 2 * totalM * N <= e->lay.part_cap)
       S *= 2;
   }
   a.S = S;

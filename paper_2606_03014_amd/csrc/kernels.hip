@@ -286,149 +286,132 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(float* __restrict__ x, con
 // 16x16x32 operand layout (lane l of 64): A = rows l%16, k = 8*(l/16)..+8;
 // B = column l%16, same k; D = column l%16, rows 4*(l/16)..+4.
 //
-// --------------------------------------- bf16 GEMM, workgroup-tile variant
-// A workgroup (4 wavefronts) owns 16*MT rows x 64*NT columns x one k-split.
-// Per stage of 4 MFMA k-steps (128 k) the split-bf16 activation block (both
-// planes) is staged in LDS in MFMA A-fragment order (1 KB lane-ordered
-// fragments, so every LDS read and write is contiguous) and shared by the four
-// wavefronts; each wavefront streams its own NT weight tiles of 16 columns
-// from HBM. LDS is double-buffered with one barrier per stage, and the next
-// stage's activation and weight loads are issued before the current stage's
-// MFMAs, so HBM latency overlaps compute. Workgroup ids are remapped so that
-// the row blocks sharing weight tiles run on the same XCD (shared L2).
-template <int MT, int NT, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_wg(GemmArgs a, int nwg) {
-  constexpr int UK = 4;                              // k-steps per stage
-  constexpr int UNITS = 2 * MT * UK * 64;            // 16-byte units per stage (both planes)
-  constexpr int PER = UNITS / 256;                   // per thread
-  __shared__ __align__(16) unsigned char sA[2][UNITS * 16];
-  const int per = (nwg + 7) / 8;
+// ------------------------------------------ bf16 GEMM, small row counts
+// Up to 16 rows per model (and, at 64 rows per chunk, the widths and grids the
+// medium-M kernel below does not take): the launch is a stream of weights that
+// nothing but latency should slow down.
+//  * A workgroup owns 16 * MT rows x 16 * CT columns of one k-split, and its
+//    four waves a quarter of that split's k each; their sums meet in LDS in
+//    fixed order. Splitting k inside the workgroup is what lets a wave own so
+//    few columns: enough workgroups to keep every CU's loads in flight, without
+//    the partial sums of as many k-splits (4 instead of 16, which the next
+//    kernel would read back).
+//  * No LDS staging and no barrier in the k loop: weights and activation
+//    fragments go straight to registers, D k-steps ahead, the same loads every
+//    step (clamped to the last), so the waits stay exact. The activations come
+//    from L2; weights are read once and loaded non-temporally (4-8% faster).
+//  * PACK (at most 8 rows): rows 0-7 of the MFMA's A operand are the hi plane,
+//    rows 8-15 the lo plane of the same rows, so one MFMA and one 1 KB activation
+//    read per weight fragment do the work of two; the halves are added at the end.
+//  * Workgroup ids are remapped so that each XCD streams one contiguous range
+//    of columns (8B gate-up at 1 row: 44.5 -> 38.4 us against the plain order) and
+//    row chunks sharing weights run side by side on it.
+// Cold weights, us per launch, before (LDS-staged workgroup tiles with up to 16
+// k-splits) -> now: 8B gate-up 47.9 -> 38.4 at 1 row, 50.0 -> 42.2 at 16; 8B down
+// 24.5 -> 19.8, 25.7 -> 22.5; 8B qkv 10.8 -> 9.7, 11.8 -> 12.9 (its four partials
+// instead of 16 save more than that in the RoPE launch); 1B gate-up 23.7 -> 12.6,
+// 25.4 -> 13.5; 1B gate-up at 64 rows 42 -> 25; three 8B models at 1 row: gate-up
+// 125 -> 106, down 61 -> 53, qkv 29.6 -> 24.3.
+__device__ __forceinline__ u32x4 load_stream(const u32x4* p) { return __builtin_nontemporal_load(p); }
+
+template <int MT, int CT, int D, int EPI, bool PACK, int WPE>
+__global__ __launch_bounds__(256, WPE) void k_gemm_sm(GemmArgs a, int nblk, int item_cols) {
+  constexpr int AP = PACK ? 1 : 2 * MT;              // activation fragments per k-step
+  __shared__ float red[4][MT * CT][256];
+  const int per = (nblk + 7) / 8;
   const int blk = (blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (blk >= a.total_items) return;
+  if (blk >= nblk) return;
+  const int sub = item_cols / (16 * CT);             // workgroups per item
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const void* Wg = a.g[0].W;
   int row0 = a.g[0].row0, nrows = a.g[0].nrows, n_mc = a.g[0].n_mc, item0 = a.g[0].item0;
 #pragma unroll
   for (int i = 1; i < kMaxGroups; ++i) {
-    if (i < a.ngroups && a.g[i].item0 <= blk) {
+    if (i < a.ngroups && a.g[i].item0 * sub <= blk) {
       Wg = a.g[i].W; row0 = a.g[i].row0; nrows = a.g[i].nrows; n_mc = a.g[i].n_mc; item0 = a.g[i].item0;
     }
   }
-  const int idx = blk - item0;
+  // a group's workgroups: ((column block, split), column sub-block), row chunk fastest
+  int idx = blk - item0 * sub;
   const int mc = idx % n_mc;
-  const int rest = idx / n_mc;
-  const int s = rest % a.S;
-  const int nb = rest / a.S;
-  const int ks0 = s * a.ksteps;
-  const int nt0 = (nb * 4 + w) * NT;                 // this wavefront's first 16-column tile
+  idx /= n_mc;
+  const int sb = idx % sub;
+  idx /= sub;
+  const int s = idx % a.S, nb = idx / a.S;
+  const int tile0 = (nb * sub + sb) * CT;            // first 16-column tile
   const int KS = a.K >> 5;
-  const u32x4* wp = (const u32x4*)Wg + ((size_t)nt0 * KS + ks0) * 64 + lane;
-  const size_t wt = (size_t)KS * 64;                 // u32x4 distance between tiles
-  const int rbase = row0 + mc * MT * 16;
-  const int rend = row0 + nrows;
-
-  // Staging: unit u = t + 256*i is lane ln = u % 64 of fragment (plane p,
-  // m-tile mt, k-step ku) = (u / (MT*UK*64), (u / (UK*64)) % MT, (u / 64) % UK):
-  // row 16*mt + ln % 16, k = 32*ku + 8*(ln / 16) .. +8 of that plane.
-  const uint16_t* X = (const uint16_t*)a.X;
-  size_t xoff[PER];
+  const int k0 = (w * a.ksteps) >> 2, nk = (((w + 1) * a.ksteps) >> 2) - k0;   // >= 1: ksteps % 4 == 0
+  const int ks0 = s * a.ksteps + k0;
+  const int rbase = row0 + mc * MT * 16, rend = row0 + nrows;
+  const u32x4* bp = (const u32x4*)Wg + ((size_t)tile0 * KS + ks0) * 64 + lane;
+  const size_t wt = (size_t)KS * 64;                 // u32x4 between weight tiles
+  const int r16 = lane & 15;
+  const uint16_t* ap[AP];
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int u = threadIdx.x + 256 * i;
-    const int ln = u & 63, ku = (u >> 6) % UK, mt = (u / (UK * 64)) % MT, p = u / (MT * UK * 64);
-    const int r = min(rbase + mt * 16 + (ln & 15), rend - 1);
-    xoff[i] = (size_t)p * a.x_lo + (size_t)r * a.K + (size_t)ks0 * 32 + ku * 32 + (ln >> 4) * 8;
+  for (int m = 0; m < AP; ++m) {
+    const int row = PACK ? min(rbase + (r16 & 7), rend - 1) : min(rbase + 16 * (m >> 1) + r16, rend - 1);
+    const size_t pl = PACK ? (size_t)(r16 >> 3) * a.x_lo : (size_t)(m & 1) * a.x_lo;
+    ap[m] = (const uint16_t*)a.X + pl + (size_t)row * a.K + (size_t)ks0 * 32 + 8 * (lane >> 4);
   }
-
-  f32x4_t acc[MT][NT];
+  u32x4 b[D][CT], av[D][AP];
+  auto load = [&](int st, int d) {
+#pragma unroll
+    for (int j = 0; j < CT; ++j) b[d][j] = load_stream(bp + j * wt + (size_t)st * 64);
+#pragma unroll
+    for (int m = 0; m < AP; ++m) av[d][m] = *(const u32x4*)(ap[m] + st * 32);
+  };
+  f32x4_t acc[MT][CT];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) acc[m][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  u32x4 stg[PER], b[UK][NT];
+    for (int j = 0; j < CT; ++j) acc[m][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto mul = [&](int d) {
 #pragma unroll
-  for (int i = 0; i < PER; ++i) stg[i] = *(const u32x4*)(X + xoff[i]);
+    for (int m = 0; m < AP; ++m)
 #pragma unroll
-  for (int u = 0; u < UK; ++u)
+      for (int j = 0; j < CT; ++j)
+        acc[m / 2][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[d][m]),
+                                                                __builtin_bit_cast(bf16x8_t, b[d][j]), acc[m / 2][j], 0, 0, 0);
+  };
 #pragma unroll
-    for (int j = 0; j < NT; ++j) b[u][j] = wp[j * wt + u * 64];
+  for (int d = 0; d < D; ++d) load(min(d, nk - 1), d);
+  int st = 0;
+  for (; st + D < nk; st += D) {
 #pragma unroll
-  for (int i = 0; i < PER; ++i) *(u32x4*)(sA[0] + (threadIdx.x + 256 * i) * 16) = stg[i];
-  __syncthreads();
-
-  const int nstage = a.ksteps / UK;
-  for (int st = 0; st < nstage; ++st) {
-    const int cur = st & 1;
-    const bool more = st + 1 < nstage;
-    u32x4 bn[UK][NT];
-    if (more) {                                       // next stage: activations and weights
-      const size_t ko = (size_t)(st + 1) * UK * 32;
-#pragma unroll
-      for (int i = 0; i < PER; ++i) stg[i] = *(const u32x4*)(X + xoff[i] + ko);
-#pragma unroll
-      for (int u = 0; u < UK; ++u)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) bn[u][j] = wp[j * wt + ((st + 1) * UK + u) * 64];
+    for (int d = 0; d < D; ++d) {
+      mul(d);
+      load(min(st + D + d, nk - 1), d);
     }
-    const unsigned char* A = sA[cur];
-#pragma unroll
-    for (int u = 0; u < UK; ++u) {
-#pragma unroll
-      for (int m = 0; m < MT; ++m) {
-        const u32x4 ah = *(const u32x4*)(A + ((0 * MT + m) * UK + u) * 1024 + lane * 16);
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-          acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ah),
-                                                              __builtin_bit_cast(bf16x8_t, b[u][j]), acc[m][j], 0, 0, 0);
-      }
-#pragma unroll
-      for (int m = 0; m < MT; ++m) {
-        const u32x4 al = *(const u32x4*)(A + ((1 * MT + m) * UK + u) * 1024 + lane * 16);
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-          acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, al),
-                                                              __builtin_bit_cast(bf16x8_t, b[u][j]), acc[m][j], 0, 0, 0);
-      }
-    }
-    if (more) {
-#pragma unroll
-      for (int i = 0; i < PER; ++i) *(u32x4*)(sA[cur ^ 1] + (threadIdx.x + 256 * i) * 16) = stg[i];
-#pragma unroll
-      for (int u = 0; u < UK; ++u)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) b[u][j] = bn[u][j];
-    }
-    __syncthreads();
   }
-
-  const int col = lane & 15;
-  const int rq = (lane >> 4) * 4;
-  if (EPI == EPI_F32) {
-    float* out = a.out + (size_t)s * a.out_split;
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+  for (int d = 0; d < D; ++d)
+    if (st + d < nk) mul(d);
+  // register i of lane l of a tile is row 4 (l / 16) + i, column l % 16
 #pragma unroll
-      for (int j = 0; j < NT; ++j)
+  for (int t = 0; t < MT * CT; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = rbase + m * 16 + rq + i;
-          if (r < rend) out[(size_t)r * a.N + (nt0 + j) * 16 + col] = acc[m][j][i];
-        }
-  } else {
-    const int half = a.N >> 1;
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-      for (int p = 0; p < NT / 2; ++p)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = rbase + m * 16 + rq + i;
-          if (r < rend) {
-            const float g = acc[m][2 * p][i], u = acc[m][2 * p + 1][i];
-            store_split(a.hout, a.h_lo, (size_t)r * half + ((nt0 >> 1) + p) * 16 + col, g / (1.f + __expf(-g)) * u);
-          }
-        }
+    for (int i = 0; i < 4; ++i) red[w][t][i * 64 + lane] = acc[t / CT][t % CT][i];
+  __syncthreads();
+  constexpr int NT = EPI == EPI_SWIGLU ? MT * CT / 2 : MT * CT;   // output tiles
+  constexpr int PER = PACK ? 128 : 256;                           // outputs of a tile
+  for (int u = threadIdx.x; u < NT * PER; u += 256) {
+    const int t = u / PER, rr = (u % PER) >> 4, col = u & 15;
+    const int row = rbase + 16 * (EPI == EPI_SWIGLU ? t / (CT / 2) : t / CT) + rr;
+    if (row >= rend) continue;
+    const int e = (rr & 3) * 64 + (rr >> 2) * 16 + col;
+    auto sum = [&](int k) {
+      float y = (red[0][k][e] + red[1][k][e]) + (red[2][k][e] + red[3][k][e]);
+      if (PACK) y += (red[0][k][e + 32] + red[1][k][e + 32]) + (red[2][k][e + 32] + red[3][k][e + 32]);   // row + 8
+      return y;
+    };
+    if (EPI == EPI_F32) {
+      a.out[(size_t)s * a.out_split + (size_t)row * a.N + (tile0 + t % CT) * 16 + col] = sum(t);
+    } else {
+      // tiles (2p, 2p+1) are (gate, up) of the same 16 hidden units
+      const int m = t / (CT / 2), p = t % (CT / 2);
+      const float g = sum(m * CT + 2 * p), up = sum(m * CT + 2 * p + 1);
+      store_split(a.hout, a.h_lo, (size_t)row * (a.N >> 1) + ((tile0 >> 1) + p) * 16 + col, g / (1.f + __expf(-g)) * up);
+    }
   }
 }
 
@@ -1529,21 +1512,30 @@ hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, in
     return hipErrorInvalidValue;
   }
   if (bf16 && mt >= kWgTile) {
-    if (a.ksteps % 4 != 0) return hipErrorInvalidValue;   // the kernel consumes k in stages of 4 steps
     const int m = mt - kWgTile;          // rows / 16
-    const int nwg = a.total_items;
-    const int grid = (nwg + 7) / 8 * 8;
-    const dim3 g(grid), b(256);
-#define WGL(M_, N_, E_) klaunch(k_gemm_wg<M_, N_, E_>, g, b, st, a, nwg)
-    if (epi == EPI_SWIGLU) {
-      if (nt == 4) { if (m == 1) WGL(1, 4, EPI_SWIGLU); else if (m == 2) WGL(2, 4, EPI_SWIGLU); else WGL(4, 4, EPI_SWIGLU); }
-      else { if (m == 1) WGL(1, 2, EPI_SWIGLU); else if (m == 2) WGL(2, 2, EPI_SWIGLU); else WGL(4, 2, EPI_SWIGLU); }
+    // every wave takes a quarter of a split, in whole k-steps
+    if (a.ksteps < 4 || a.ksteps % 4 != 0 || nt < 1 || a.N % (64 * nt) != 0) return hipErrorInvalidValue;
+    auto go = [&](auto kern, int cols) {
+      const int nblk = a.total_items * (64 * nt / cols);
+      klaunch(kern, dim3((nblk + 7) / 8 * 8), dim3(256), st, a, nblk, 64 * nt);
+    };
+    if (m == 1 && nt == 2) {
+      for (int g = 0; g < a.ngroups; ++g)
+        if (a.g[g].nrows > 8) return hipErrorInvalidValue;
+      if (epi == EPI_SWIGLU) go(k_gemm_sm<1, 2, 4, EPI_SWIGLU, true, 4>, 32);
+      else go(k_gemm_sm<1, 2, 4, EPI_F32, true, 4>, 32);
+    } else if (m == 1 && nt == 4) {
+      if (epi == EPI_SWIGLU) go(k_gemm_sm<1, 4, 2, EPI_SWIGLU, false, 4>, 64);
+      else go(k_gemm_sm<1, 4, 2, EPI_F32, false, 4>, 64);
+    } else if (m == 2 && nt == 2) {
+      if (epi == EPI_SWIGLU) go(k_gemm_sm<2, 4, 2, EPI_SWIGLU, false, 3>, 64);
+      else go(k_gemm_sm<2, 4, 2, EPI_F32, false, 3>, 64);
+    } else if (m == 4 && nt == 2) {
+      if (epi == EPI_SWIGLU) go(k_gemm_sm<4, 4, 2, EPI_SWIGLU, false, 2>, 64);
+      else go(k_gemm_sm<4, 4, 2, EPI_F32, false, 2>, 64);
     } else {
-      if (nt == 4) { if (m == 1) WGL(1, 4, EPI_F32); else if (m == 2) WGL(2, 4, EPI_F32); else WGL(4, 4, EPI_F32); }
-      else if (nt == 2) { if (m == 1) WGL(1, 2, EPI_F32); else if (m == 2) WGL(2, 2, EPI_F32); else WGL(4, 2, EPI_F32); }
-      else { if (m == 1) WGL(1, 1, EPI_F32); else if (m == 2) WGL(2, 1, EPI_F32); else WGL(4, 1, EPI_F32); }
+      return hipErrorInvalidValue;
     }
-#undef WGL
     return hipGetLastError();
   }
   if (!bf16) {

@@ -91,3 +91,22 @@ def test_device_filled_histories_equal_uploaded_ones(dtype, hd, seats):
         assert np.array_equal(got[0][1][i], got[1][1][i]), f"history of {ctxs[i]}: logits differ"
     for a, b in zip(got[0][0], got[1][0]):
         assert np.array_equal(a, b)
+
+
+# small-M GEMM: 1, 8 (both planes packed in one MFMA), 9, 16, 17, 32 and 33 rows per model beside a smaller model; K of
+# 2 to 11 k-steps per wave (ffn 1408 splits neither way), a qkv width that is no multiple of 256 (384), and the
+# four-way split next to none
+@pytest.mark.parametrize("rows", [(1,), (8, 3), (9, 2), (16, 1), (17, 8), (32,), (33, 5), (64, 16), (65,)])
+@pytest.mark.parametrize("d,ffn,nh,nkv", [(256, 1408, 4, 1), (1024, 512, 2, 2), (512, 128, 8, 2)])
+def test_bf16_gemm_small_rows(rows, d, ffn, nh, nkv):
+    shape = ModelShape(n_layers=1, d_model=d, n_heads=nh, n_kv_heads=nkv, head_dim=64, ffn_dim=ffn, vocab=1152)
+    ws = [generate_weights(shape, "bf16", d + ffn, 97, m) for m in range(len(rows))]
+    rng = np.random.default_rng(list(rows))
+    reqs = [(rng.integers(0, shape.vocab, 1 + (i % 3)).astype(np.int32), m, 2) for m, r in enumerate(rows)
+            for i in range(r)]
+    consts = EngineConsts(num_kv_blocks=256, max_num_seqs=96, max_prefill_tokens=256, max_model_len=64)
+    toks, logs = run_requests(shape, "bf16", consts, ws, reqs)
+    for i in sorted({0, 1, 7, 8, len(reqs) // 2, len(reqs) - 2, len(reqs) - 1}):
+        if 0 <= i < len(reqs):
+            compare(shape, ws[reqs[i][1]], reqs[i][0], toks[i], logs[i], True, 2e-2, what=f"{rows} call {i}",
+                    report_pure=False)
