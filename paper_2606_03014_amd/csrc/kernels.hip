@@ -13,6 +13,7 @@
 #include <climits>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 namespace moa {
 
@@ -453,12 +454,10 @@ __device__ __forceinline__ void ds_write_b32(unsigned addr, unsigned v) {
 // Wait for every outstanding LDS access; tying v makes its later uses follow.
 __device__ __forceinline__ void lgkm_wait_for(u32x4& v) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v)); }
 
-// ----------------------------- medium- and large-M GEMM (16x16x32 MFMA)
-// From a few dozen rows per model up to prefill chunks of many thousands.
-// At decode sizes every weight byte feeds only that many rows of MFMA work,
-// so the GEMM must stream the weights at HBM speed; at prefill sizes it is
-// bound by the matrix cores, and keeping the weights out of LDS leaves the
-// LDS to the activations. A workgroup of NW waves owns one row chunk of a
+// -------------------------------------- medium-M GEMM (16x16x32 MFMA)
+// A few dozen to a few hundred rows per model. Every weight byte feeds only that
+// many rows of MFMA work, so the GEMM must stream the weights at HBM speed, and
+// keeping the weights out of LDS leaves the LDS to the activations. A workgroup of NW waves owns one row chunk of a
 // group (mrows rows, at most 16*RT: a group of up to that many rows is one
 // chunk, so each weight tile leaves HBM once per step; a larger group is cut
 // into chunks whose items for one column block run side by side on one XCD)
@@ -627,6 +626,166 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs a, int nwg) {
     }
   }
   wait_vmcnt<0>();                                   // no load may land in LDS after the workgroup ends
+
+  const int col = lane & 15;
+  const int rq = (lane >> 4) * 4;
+  if (EPI == EPI_F32) {
+    float* out = a.out + (size_t)s * a.out_split;
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = rbase + r * 16 + rq + i;
+          if (row < rend) out[(size_t)row * a.N + (nt0 + c) * 16 + col] = acc[r][c][i];
+        }
+  } else {
+    // tiles (2p, 2p+1) are (gate, up) of the same 16 hidden units
+    const int half = a.N >> 1;
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int q = 0; q < CT / 2; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = rbase + r * 16 + rq + i;
+          if (row < rend) {
+            const float g = acc[r][2 * q][i], u = acc[r][2 * q + 1][i];
+            store_split(a.hout, a.h_lo, (size_t)row * half + ((nt0 >> 1) + q) * 16 + col, g / (1.f + __expf(-g)) * u);
+          }
+        }
+  }
+}
+
+// ------------------------------------------- large-M GEMM (16x16x32 MFMA)
+// Prefill chunks and wide decode batches are bound by the matrix cores. Same
+// tiles as the medium-M kernel at RT = 8 (128 rows x 8 waves of 16 * CT columns,
+// the same products in the same order), fed so that the MFMAs need not wait:
+//  * activations go through registers into a two-slot LDS ring (loaded a stage
+//    before they are written, written a stage before they are read), so the
+//    compiler can follow every LDS access and no read waits for a load in flight;
+//  * a stage's 16 fragment reads are spread between its MFMAs by scheduling
+//    groups: eight reads ahead, then one read per CT MFMAs. With all of a plane's
+//    reads and one wait in front of its 32 MFMAs the matrix cores were 64% busy.
+// Same clocks, same launches: 8B qkv at 2,048 rows 184 -> 166 us, o 109 -> 105,
+// gate-up 764 -> 736, down 350 -> 336; at 8,192 rows gate-up 2,920 -> 2,779 (692
+// TFLOP/s useful, twice that on the MFMA for the split activations). Measured and
+// not kept: 32x32x16 MFMAs (5-10% slower), 64-row waves over 128 columns
+// (10-20%), two 4-wave workgroups per CU (12-18%), raised wave priority (8-10%).
+template <int CT, int EPI>
+__global__ __launch_bounds__(512, 2) void k_gemm_big(GemmArgs a, int nwg) {
+  constexpr int RT = 8, NW = 8, D = 3;
+  constexpr unsigned SLOT = 2 * RT * 1024;
+  __shared__ __align__(1024) unsigned char smem[2 * SLOT];
+  const int per = (nwg + 7) / 8;
+  const int blk = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (blk >= a.total_items) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const void* Wg = a.g[0].W;
+  int row0 = a.g[0].row0, nrows = a.g[0].nrows, n_mc = a.g[0].n_mc, item0 = a.g[0].item0, mrows = a.g[0].mrows;
+#pragma unroll
+  for (int i = 1; i < kMaxGroups; ++i) {
+    if (i < a.ngroups && a.g[i].item0 <= blk) {
+      Wg = a.g[i].W; row0 = a.g[i].row0; nrows = a.g[i].nrows; n_mc = a.g[i].n_mc; item0 = a.g[i].item0;
+      mrows = a.g[i].mrows;
+    }
+  }
+  const int ncol = a.N / (NW * CT * 16);
+  const int idx = blk - item0;
+  const int mc = idx % n_mc;
+  const int nb = (idx / n_mc) % ncol;
+  const int s = idx / (n_mc * ncol);
+  const int KS = a.K >> 5;
+  const int ks0 = (s * KS) / a.S, nk = ((s + 1) * KS) / a.S - ks0;
+  const int crows = mrows > 0 ? mrows : RT * 16;
+  const int rbase = row0 + mc * crows;
+  const int rend = min(row0 + nrows, rbase + crows);
+  const int nrt = min(RT, (rend - rbase + 15) >> 4); // row tiles holding rows; the rest are not multiplied
+  const int nt0 = (nb * NW + w) * CT;                // this wave's first 16-column weight tile
+
+  const unsigned char* asrc[2];                      // this wave's two of the stage's 16 fragments
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int f = w * 2 + i, p = f / RT, r = f % RT;
+    const int row = min(rbase + 16 * r + (lane & 15), rend - 1);
+    asrc[i] = (const unsigned char*)((const uint16_t*)a.X + (size_t)p * a.x_lo + (size_t)row * a.K +
+                                     (size_t)ks0 * 32 + 8 * (lane >> 4));
+  }
+  const u32x4* bsrc = (const u32x4*)Wg + ((size_t)nt0 * KS + ks0) * 64 + lane;
+  const size_t btile = (size_t)KS * 64;              // u32x4 between weight tiles
+  u32x4 ga[2], b[D][CT];
+  auto loadA = [&](int st) {
+    const size_t o = (size_t)min(st, nk - 1) * 64;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) ga[i] = *(const u32x4*)(asrc[i] + o);
+  };
+  auto writeA = [&](int st) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) *(u32x4*)(smem + (st & 1) * SLOT + (w * 2 + i) * 1024 + lane * 16) = ga[i];
+  };
+  auto loadB = [&](int st, u32x4* dst) {
+    const size_t o = (size_t)min(st, nk - 1) * 64;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) dst[c] = bsrc[c * btile + o];
+  };
+  // LDS only: the loads in flight stay in flight
+  auto barrier = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  f32x4_t acc[RT][CT];
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int c = 0; c < CT; ++c) acc[r][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  loadA(0);
+#pragma unroll
+  for (int d = 0; d < D; ++d) loadB(d, b[d]);
+  writeA(0);
+  loadA(1);
+  barrier();
+  // Stage st reads slot st & 1 while the other slot takes stage st + 1; the one
+  // barrier per stage makes that slot visible and frees the one just read.
+  auto loop = [&](auto full) {
+    for (int st0 = 0; st0 < nk; st0 += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int st = st0 + d;
+        if (st >= nk) break;
+        const unsigned char* sl = smem + (st & 1) * SLOT + lane * 16;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            if (!full.value && r >= nrt) continue;
+            const u32x4 av = *(const u32x4*)(sl + (p * RT + r) * 1024);
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+              acc[r][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av),
+                                                                  __builtin_bit_cast(bf16x8_t, b[d][c]), acc[r][c], 0, 0, 0);
+          }
+          if (p == 0) {
+            writeA(st + 1);
+            loadA(st + 2);
+          }
+        }
+        loadB(st + D, b[d]);
+        if (full.value) {
+          __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);      // LDS reads
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x008, CT, 0);   // MFMAs
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          }
+        }
+        barrier();
+      }
+    }
+  };
+  if (nrt == RT) loop(std::true_type{});
+  else loop(std::false_type{});
 
   const int col = lane & 15;
   const int rq = (lane >> 4) * 4;
@@ -1475,8 +1634,15 @@ static hipError_t gemm_mm(hipStream_t st, const GemmArgs& a) {
   return hipGetLastError();
 }
 
-// nt: CT (4 waves), 8 + CT (8 waves) or 16 + CT (8 waves, weight ring three
-// stages deep); see kMmTile
+template <int CT, int EPI>
+static hipError_t gemm_big(hipStream_t st, const GemmArgs& a) {
+  const int nwg = a.total_items;
+  klaunch(k_gemm_big<CT, EPI>, dim3((nwg + 7) / 8 * 8), dim3(512), st, a, nwg);
+  return hipGetLastError();
+}
+
+// nt: CT (4 waves), 8 + CT (8 waves) or 16 + CT (8 waves, large-M kernel or a
+// three-stage weight ring); see kMmTile
 template <int RT, int EPI>
 static hipError_t gemm_mm_nt(hipStream_t st, const GemmArgs& a, int nt) {
   if constexpr (RT <= 4)                          // 4 waves x RT = 8 x CT = 4: one wave per SIMD
@@ -1485,8 +1651,17 @@ static hipError_t gemm_mm_nt(hipStream_t st, const GemmArgs& a, int nt) {
   if constexpr (RT >= 4) {
     if (nt == 12) return gemm_mm<RT, 4, 8, (RT >= 8 ? 2 : 3), EPI>(st, a);
     if constexpr (RT >= 8) {
-      if (nt == 10 || nt == 18) return gemm_mm<RT, 2, 8, 3, EPI>(st, a);
-      if (nt == 20) return gemm_mm<RT, 4, 8, 3, EPI>(st, a);
+      if (nt == 10) return gemm_mm<RT, 2, 8, 3, EPI>(st, a);
+      if (nt == 18 || nt == 20) {
+        // whole 128-row chunks: the large-M kernel. Shorter ones (medium-row
+        // gate-up) keep the medium-M kernel, which skips padding tiles without
+        // losing its schedule (8B gate-up at 110/90/60 rows: 177 us, 190 on the
+        // other). Both give the same bits.
+        bool whole = true;
+        for (int g = 0; g < a.ngroups; ++g) whole = whole && a.g[g].mrows == 128;
+        if (whole) return nt == 18 ? gemm_big<2, EPI>(st, a) : gemm_big<4, EPI>(st, a);
+        if constexpr (EPI == EPI_SWIGLU) return nt == 18 ? gemm_mm<RT, 2, 8, 3, EPI>(st, a) : gemm_mm<RT, 4, 8, 3, EPI>(st, a);
+      }
     }
   }
   return hipErrorInvalidValue;

@@ -110,3 +110,13 @@ def test_bf16_gemm_small_rows(rows, d, ffn, nh, nkv):
         if 0 <= i < len(reqs):
             compare(shape, ws[reqs[i][1]], reqs[i][0], toks[i], logs[i], True, 2e-2, what=f"{rows} call {i}",
                     report_pure=False)
+
+
+# large-M GEMM: one chunk of 128 rows and a part, K of two k-steps (ffn 128 in 8 columns' worth), k-splits of uneven length,
+# 256- and 512-column tiles, a second model with a few rows in the same launches
+@pytest.mark.parametrize("rows", [(256,), (257, 3), (385,), (300, 290)])
+@pytest.mark.parametrize("d,ffn", [(256, 128), (1024, 768)])
+def test_bf16_gemm_large_rows(rows, d, ffn):
+    shape = ModelShape(n_layers=1, d_model=d, n_heads=4, n_kv_heads=2, head_dim=64, ffn_dim=ffn, vocab=512)
+    consts = EngineConsts(num_kv_blocks=256, max_num_seqs=8, max_prefill_tokens=1024, max_model_len=512)
+    _check(shape, "bf16", rows, 2, seed=sum(rows) + d, models=len(rows), consts=consts)
