@@ -416,6 +416,173 @@ __global__ __launch_bounds__(256, WPE) void k_gemm_sm(GemmArgs a, int nblk, int 
   }
 }
 
+// -------------------------------- row GEMMs of steps with very few rows
+// Up to 8 rows per model, a layer of nine launches spends as long on launches
+// and the short kernels between the GEMMs (5 us each for a norm or RoPE) as on the
+// 1B weights. Here no k-split crosses a workgroup (NW waves split k, 16 * CT columns
+// each, as in the small-M kernel with both planes packed), so the epilogue
+// holds finished sums and does the next kernel's work on them:
+//  * O and down add the residual and write x, x * gamma of the next norm as a
+//    split pair, and each 16 columns' sum of squares;
+//  * the consumer multiplies that pair unnormalised and scales its sums by the
+//    row's rsqrt(mean square): the scale commutes with the product;
+//  * qkv owns both halves of its rotation pairs (tiles hd / 2 columns apart).
+// A layer is then qkv, attention (and its combine), O, gate-up, down. Without the
+// cross-workgroup split the GEMMs lose 0-1 us each at 1 row and up to 7 at 8
+// (8B down 20 -> 27 us), against ~15 us saved per layer.
+template <int CT, int NW, int D, int EPI>
+__global__ __launch_bounds__(64 * NW, 4) void k_gemm_row(GemmArgs a, RowArgs f, int ncb) {
+  __shared__ float red[NW][CT][256];
+  __shared__ float rs[kRowMax];
+  const int nblk = ncb * a.ngroups;
+  const int per = (nblk + 7) / 8;
+  const int blk = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (blk >= nblk) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int g = blk / ncb, cb = blk - g * ncb;
+  const void* Wg = a.g[0].W;
+  const void* gam = f.gamma.p[0];
+  int row0 = a.g[0].row0, nrows = a.g[0].nrows;
+#pragma unroll
+  for (int i = 1; i < kMaxGroups; ++i)
+    if (i == g) { Wg = a.g[i].W; row0 = a.g[i].row0; nrows = a.g[i].nrows; gam = f.gamma.p[i]; }
+  const int KS = a.K >> 5;
+  const int ks0 = (w * KS) / NW, nk = ((w + 1) * KS) / NW - ks0;
+  int tile[CT];
+  int head = 0, j0 = 0;
+  if constexpr (EPI == ROW_ROPE) {
+    const int per_head = f.hd / 32;
+    head = cb / per_head;
+    const int u = cb - head * per_head;
+    j0 = u * 16;
+    tile[0] = head * (f.hd / 16) + u;
+    tile[CT - 1] = tile[0] + per_head;
+  } else {
+#pragma unroll
+    for (int c = 0; c < CT; ++c) tile[c] = cb * CT + c;
+  }
+  // the rows' scales: a part of each wave's lanes sums a row's 16-column squares
+  if constexpr (EPI != ROW_RES) {
+    constexpr int LPR = 64 * NW / kRowMax;            // lanes per row (32 or 64)
+    const int r = threadIdx.x / LPR, l = threadIdx.x % LPR;
+    float t = 0.f;
+    const int n = f.d >> 4;
+    if (f.ss_in && r < nrows)
+      for (int i = l; i < n; i += LPR) t += f.ss_in[(size_t)(row0 + r) * n + i];
+    t = sum16(t);
+    t += swz_xor16(t);
+    if constexpr (LPR == 64) t += __shfl_xor(t, 32, 64);
+    if (l == 0) rs[r] = f.ss_in ? rsqrtf(t / (float)f.d + f.eps) : 1.f;
+  }
+  const u32x4* bp[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) bp[c] = (const u32x4*)Wg + ((size_t)tile[c] * KS + ks0) * 64 + lane;
+  const int r16 = lane & 15;
+  const uint16_t* ap = (const uint16_t*)a.X + (size_t)(r16 >> 3) * a.x_lo +
+                       (size_t)(row0 + min(r16 & 7, nrows - 1)) * a.K + (size_t)ks0 * 32 + 8 * (lane >> 4);
+  f32x4_t acc[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  if (nk > 0) {                                       // wave-uniform
+    u32x4 b[D][CT], av[D];
+    auto load = [&](int st, int d) {
+#pragma unroll
+      for (int c = 0; c < CT; ++c) b[d][c] = load_stream(bp[c] + (size_t)st * 64);
+      av[d] = *(const u32x4*)(ap + st * 32);
+    };
+    auto mul = [&](int d) {
+#pragma unroll
+      for (int c = 0; c < CT; ++c)
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[d]),
+                                                         __builtin_bit_cast(bf16x8_t, b[d][c]), acc[c], 0, 0, 0);
+    };
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(min(d, nk - 1), d);
+    int st = 0;
+    for (; st + D < nk; st += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        mul(d);
+        load(min(st + D + d, nk - 1), d);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (st + d < nk) mul(d);
+  }
+#pragma unroll
+  for (int c = 0; c < CT; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) red[w][c][i * 64 + lane] = acc[c][i];
+  __syncthreads();
+  if (threadIdx.x >= 16 * kRowMax) return;            // whole waves
+  const int rr = threadIdx.x >> 4, col = threadIdx.x & 15;
+  const bool live = rr < nrows;
+  const int row = row0 + rr;
+  const int e = (rr & 3) * 64 + (rr >> 2) * 16 + col; // hi plane; the lo plane's row + 8 is 32 further
+  float y[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    float v[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) v[k] = red[k][c][e] + red[k][c][e + 32];
+#pragma unroll
+    for (int k = NW / 2; k > 0; k /= 2)
+#pragma unroll
+      for (int i = 0; i < k; ++i) v[i] += v[i + k];
+    y[c] = v[0];
+  }
+  if constexpr (EPI == ROW_RES) {
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const int n = tile[c] * 16 + col;
+      const size_t o = (size_t)row * f.d + n;
+      float v = 0.f;
+      if (live) {
+        v = f.x[o] + y[c];
+        f.x[o] = v;
+        store_split(f.xn, f.xn_lo, o, v * bf2f(((const uint16_t*)gam)[n]));
+      }
+      const float t = sum16(v * v);
+      if (live && col == 0) f.ss[(size_t)row * (f.d >> 4) + tile[c]] = t;
+    }
+  } else if constexpr (EPI == ROW_SWIGLU) {
+    if (live) {
+#pragma unroll
+      for (int p = 0; p < CT / 2; ++p) {
+        const float gt = y[2 * p] * rs[rr], up = y[2 * p + 1] * rs[rr];
+        store_split(a.hout, a.h_lo, (size_t)row * (a.N >> 1) + (tile[2 * p] >> 1) * 16 + col,
+                    gt / (1.f + __expf(-gt)) * up);
+      }
+    }
+  } else if (live) {
+    const int half = f.hd >> 1, jj = j0 + col;
+    const float x1 = y[0] * rs[rr], x2 = y[CT - 1] * rs[rr];
+    const int pos = f.row_pos[row];
+    const size_t hs = (size_t)2 * kBlock * f.hd;
+    if (head < f.n_h + f.n_kv) {
+      const float2 cs = f.rope_tab[(size_t)pos * half + jj];
+      const float y1 = x1 * cs.x - x2 * cs.y, y2 = x2 * cs.x + x1 * cs.y;
+      if (head < f.n_h) {
+        const size_t o = ((size_t)row * f.n_h + head) * f.hd + jj;
+        f.q[o] = y1;
+        f.q[o + half] = y2;
+      } else {
+        const int b = f.bt_store[f.row_bt[row] + (pos >> 4)];
+        const size_t o = (((size_t)f.layer * f.num_blocks + b) * f.n_kv + (head - f.n_h)) * hs + (pos & 15) * f.hd + jj;
+        ((uint16_t*)f.kv)[o] = f2bf(y1);
+        ((uint16_t*)f.kv)[o + half] = f2bf(y2);
+      }
+    } else {
+      const int b = f.bt_store[f.row_bt[row] + (pos >> 4)];
+      const size_t o = (((size_t)f.layer * f.num_blocks + b) * f.n_kv + (head - f.n_h - f.n_kv)) * hs +
+                       (size_t)kBlock * f.hd + (pos & 15) * f.hd + jj;
+      ((uint16_t*)f.kv)[o] = f2bf(x1);
+      ((uint16_t*)f.kv)[o + half] = f2bf(x2);
+    }
+  }
+}
+
 // ---------------------------------------- wait, LDS and direct-load helpers
 // Explicit waits, LDS addressing and untracked LDS reads shared by the GEMM
 // and attention kernels below. Direct global->LDS loads
@@ -1729,6 +1896,24 @@ hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, in
     return hipGetLastError();
   }
   return hipErrorInvalidValue;                        // no bf16 kernel for this tile code
+}
+
+hipError_t launch_gemm_row(hipStream_t st, GemmArgs a, const RowArgs& f, int epi) {
+  if (a.ngroups < 1) return hipSuccess;
+  if (a.K % 32 != 0 || a.N % 32 != 0) return hipErrorInvalidValue;
+  for (int g = 0; g < a.ngroups; ++g)
+    if (a.g[g].nrows < 1 || a.g[g].nrows > kRowMax) return hipErrorInvalidValue;
+  auto go = [&](auto kern, int cols, int threads) {
+    const int ncb = a.N / cols, nblk = ncb * a.ngroups;
+    klaunch(kern, dim3((nblk + 7) / 8 * 8), dim3(threads), st, a, f, ncb);
+  };
+  // O and down own 16 columns (at d 4096 one workgroup per CU), qkv and gate-up
+  // 32; gate-up has workgroups enough without an eight-way k-split
+  if (epi == ROW_RES && a.N == f.d) go(k_gemm_row<1, 8, 4, ROW_RES>, 16, 512);
+  else if (epi == ROW_SWIGLU) go(k_gemm_row<2, 4, 4, ROW_SWIGLU>, 32, 256);
+  else if (epi == ROW_ROPE && a.N == (f.n_h + 2 * f.n_kv) * f.hd && f.hd % 32 == 0) go(k_gemm_row<2, 8, 4, ROW_ROPE>, 32, 512);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_rope_kv(hipStream_t st, bool bf16, const float* part, int nsplit, size_t split_stride,

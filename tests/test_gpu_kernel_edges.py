@@ -120,3 +120,22 @@ def test_bf16_gemm_large_rows(rows, d, ffn):
     shape = ModelShape(n_layers=1, d_model=d, n_heads=4, n_kv_heads=2, head_dim=64, ffn_dim=ffn, vocab=512)
     consts = EngineConsts(num_kv_blocks=256, max_num_seqs=8, max_prefill_tokens=1024, max_model_len=512)
     _check(shape, "bf16", rows, 2, seed=sum(rows) + d, models=len(rows), consts=consts)
+
+
+# row GEMMs (steps of up to six rows over all models) and the step on either side of that: K of 4 k-steps (fewer than the
+# eight waves that share them), both head widths, one to eight query heads per KV head, prompts of one to three tokens
+# prefilled in such steps, one model and three on two streams
+@pytest.mark.parametrize("rows", [(1,), (2, 3, 1), (6,), (7,), (4, 3)])
+@pytest.mark.parametrize("d,ffn,nh,nkv,hd", [(256, 128, 8, 1, 64), (512, 1408, 2, 2, 128), (2048, 256, 16, 8, 128)])
+def test_bf16_row_gemms(rows, d, ffn, nh, nkv, hd):
+    shape = ModelShape(n_layers=2, d_model=d, n_heads=nh, n_kv_heads=nkv, head_dim=hd, ffn_dim=ffn, vocab=512)
+    ws = [generate_weights(shape, "bf16", d + ffn, 97, m) for m in range(len(rows))]
+    rng = np.random.default_rng(list(rows))
+    reqs = [(rng.integers(0, shape.vocab, 1 + (i + m) % 3).astype(np.int32), m, 4) for m, r in enumerate(rows)
+            for i in range(r)]
+    consts = EngineConsts(num_kv_blocks=64, max_num_seqs=8, max_prefill_tokens=6, max_model_len=64)
+    toks, logs = run_requests(shape, "bf16", consts, ws, reqs)
+    one, logs1 = run_requests(shape, "bf16", consts, ws, reqs, one_stream=True)
+    for i, (p, m, _) in enumerate(reqs):
+        compare(shape, ws[m], p, toks[i], logs[i], True, 2e-2, what=f"{rows} call {i}", report_pure=False)
+        assert np.array_equal(toks[i], one[i]) and np.array_equal(logs[i], logs1[i])
