@@ -516,19 +516,12 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
   // the medium-M kernel.
   //  * Whole 16-row tiles of a group per workgroup: RT tiles per row chunk,
   //    2 up to 32 rows, 4 up to 64, else 8.
-  //  * 8 waves over 512 columns where N allows; otherwise 8 waves over 256
-  //    at RT = 8 and 4 waves over 256 below (a vocabulary of 128,256 is
-  //    501 x 256, and two 64-row chunks per model would stream its LM head
-  //    twice).
-  //  * About one workgroup per CU. F32 projections take the k-split that
-  //    brings the grid nearest ~224 workgroups; gate-up (no k-split: its
-  //    SwiGLU epilogue needs the whole sum) takes the first tile shape whose
-  //    grid has 150..256 workgroups, else the workgroup-tile kernel.
-  // Measured on 8B shapes with cold weights, three groups of 16..200 rows:
-  // 2-40% faster per projection than the workgroup-tile kernel, and
-  // bit-identical on the same split. A 4-wave, 64-row-chunk plan with
-  // three k-splits for the square O projection (its norm then reads fewer
-  // partials) measured no faster in the 3+1x8B window.
+  //  * 8 waves over 512 columns, or over 256 at RT = 8, 4 waves over 256 below (a
+  //    vocabulary of 128,256 is 501 x 256, and two 64-row chunks per model would
+  //    stream its LM head twice); F32 projections choose between them below.
+  //  * About one workgroup per CU. Gate-up (no k-split: its SwiGLU epilogue needs
+  //    the whole sum) takes the first tile shape whose grid has 150..256
+  //    workgroups, else the small-M kernel.
   if (maxM > 16 && N % 256 == 0) {
     struct Shape { int rt, nw, ct; };
     auto chunks_of = [&](int rt) {
@@ -548,11 +541,40 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
         if (items >= 150 && items <= 256) { sh = c; break; }
       }
     } else {
-      sh = (rt0 >= 4 && N % 512 == 0) ? Shape{rt0, 8, 4} : (rt0 == 8 ? Shape{8, 8, 2} : Shape{rt0, 4, 4});
+      // F32 projections: columns per workgroup and k-split together, on the sum
+      // of the GEMM and its consumer's read of the partials (cold weights; swept
+      // over 256 and 512 columns and S = 2..16 at 24 to 260 rows in one to four
+      // groups of both widths; us of plan "512 columns at ~224 workgroups" -> this):
+      //  * 512 columns (fewest activation reads) while a split keeps 20 k-steps (12
+      //    up to 64 rows, where 256 columns mean four waves, too few beside another
+      //    stream: a four-layer step of four 8B models at 60 rows 1,896 us, 2,024 with
+      //    20 there): 8B down, three models at 90/70/50 rows 93 (108 on 256 columns).
+      //  * else 256 columns and half the splits, at ~224 workgroups, or as many as
+      //    fit one per CU for a long K (past 32 rows): 8B o at 88 rows 25.1 -> 23.0, down 48.0 ->
+      //    39.9; 1B qkv of three models at 90/70/50 26.8 -> 22.6, o 23.6 -> 19.9.
+      //  * where even 16 splits of 256 columns leave CUs idle, the small-M kernel,
+      //    which splits k inside its workgroups: 1B o at 60 rows 17.9 -> 12.6, qkv
+      //    20.1 -> 14.5, down 25.9 -> 20.6; 8B o at 24 rows 17.2 -> 14.5. Not past 64
+      //    rows for a long K (1B down at 88 rows: 29.3, 24.6 here).
+      const Shape wide = (rt0 >= 4 && N % 512 == 0) ? Shape{rt0, 8, 4} : Shape{0, 0, 0};
+      const Shape narrow = rt0 == 8 ? Shape{8, 8, 2} : Shape{rt0, 4, 4};
+      const int nb_rows = chunks_of(rt0), base256 = nb_rows * (N / 256);
+      sh = wide.rt ? wide : narrow;
       if (allow_split) {
-        const int base = chunks_of(sh.rt) * (N / (16 * sh.nw * sh.ct));
-        S = std::max(1, std::min(16, (224 + base / 2) / std::max(base, 1)));
-        while (S > 1 && ((int64_t)S * totalM * N > e->lay.part_cap || S > KS)) --S;
+        auto bounded = [&](int s) {
+          s = std::max(1, std::min(16, s));
+          while (s > 1 && ((int64_t)s * totalM * N > e->lay.part_cap || s > KS)) --s;
+          return s;
+        };
+        const int base = std::max(1, nb_rows * (N / (16 * sh.nw * sh.ct)));
+        S = bounded((224 + base / 2) / base);
+        const bool idle = base256 * 16 <= (maxM <= 32 ? 256 : 192);
+        if (idle && maxM <= 128 && (K <= 4096 || maxM <= 64)) {
+          sh = Shape{0, 0, 0};
+        } else if (!wide.rt || KS < (rt0 == 8 ? 20 : 12) * S || base * 16 < 192) {
+          sh = narrow;
+          S = bounded(KS >= 256 && rt0 > 2 ? 256 / base256 : (224 + base256 / 2) / base256);
+        }
       }
     }
     if (sh.rt) {
@@ -613,9 +635,12 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
   // 8 where 4 leaves CUs idle. At least 4 k-steps per wave up to 8 rows, 2 above.
   // Swept at 1, 8, 16, 32 and 64 rows on one and three models of both widths:
   // within 5% of the best power of two but for 8B qkv at 16 rows (12.9 us, 11.6 at 8).
+  // Above 16 rows ~192 workgroups (1B o, qkv at 24 to 128 rows: the best of 1..16).
   int S = 1;
   if (allow_split) {
     int want = maxM <= 8 ? (KS >= 384 ? 2 : 4) : (base * 4 < 256 ? 8 : 4);
+    if (maxM > 16)                                   // ~192 workgroups of 64 columns
+      for (want = 1; want < 8 && base * want < 192;) want *= 2;
     const int min_k = maxM <= 8 ? 4 : 2;
     while (S < want && KS % (S * 2 * 4) == 0 && KS / (S * 2 * 4) >= min_k &&
            (int64_t)S * 2 * totalM * N <= e->lay.part_cap)
