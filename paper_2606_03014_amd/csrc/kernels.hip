@@ -1304,6 +1304,16 @@ __global__ __launch_bounds__(GQ * 64, ATTN_WPE) void k_attn(const AttnItem* __re
   }
 }
 
+// x combined with the other half-wave's (lane ^ 32), without an LDS round trip
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ __forceinline__ float add_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, x), false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
 // ------------------------------------------ causal prefill attention (MFMA)
 // Causal prefill attention on the 32x32x16 MFMA. A workgroup is one query
 // head and up to kPrefillRows consecutive positions of one request, four
@@ -1314,9 +1324,22 @@ __global__ __launch_bounds__(GQ * 64, ATTN_WPE) void k_attn(const AttnItem* __re
 // one exchange with lane l^32), and those 16 probabilities are directly the
 // B operand of O^T = V^T P^T, with the key order inside each 16-key step
 // permuted identically in A (V^T, read from LDS) and B (P^T, in registers).
-// q and P enter the MFMAs as split bf16 (hi + lo, two MFMAs each). K tiles
-// reach LDS by direct global->LDS loads into a three-stage ring, in MFMA
-// fragment order; V tiles go through registers and are stored transposed.
+// q and P enter the MFMAs as split bf16 (hi + lo, two MFMAs each). K and V tiles
+// reach LDS by direct global->LDS loads into three-stage rings, K in MFMA fragment
+// order, V in its rows, read transposed.
+// Bound by issue: per tile a wave owes 32 MFMAs and ~160 VALU instructions, and
+// the SIMD's two waves together keep the matrix cores 58% and the VALU 48% busy.
+// So both are kept short and side by side:
+//  * the next tile's scores are multiplied between this tile's softmax
+//    instructions, two MFMAs and a share of the softmax at a time, and half of P
+//    is split between the MFMAs of P V;
+//  * the scores' accumulator starts from minus the reference maximum, which saves
+//    the subtraction, and q hi and q lo share one chain, which saves an addition;
+//  * addresses: wave-uniform parts are scalar, block ids are read an iteration
+//    ahead in units of one head's block.
+// Mean launch over 9,001- and 17,003-token prompts at 32 heads of 128 (16k-row
+// chunks): 3,155 us with scores, softmax and P V one after the other, 2,995 with them
+// side by side, 2,759 with the VALU instructions per MFMA cut from 6.7 to 5.0.
 #ifndef PREFILL_WPE
 #define PREFILL_WPE 2
 #endif
@@ -1347,20 +1370,19 @@ __global__ __launch_bounds__(256, PREFILL_WPE) void k_prefill_attn(const Prefill
   const PrefillItem it = items[blockIdx.x];
   const int h = blockIdx.y;
   const int kvh = h / (n_h / n_kv);
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int c32 = lane & 31, hf = lane >> 5;
   const int kmax = it.pos0 + it.nq;          // keys [0, kmax)
   const int ntile = (kmax + TK - 1) / TK;
-  const size_t hs = (size_t)2 * kBlock * HD;
-  const uint16_t* pool = kv + ((size_t)layer * NB * n_kv + kvh) * hs;
-  const size_t bstride = (size_t)n_kv * hs;
+  constexpr unsigned HS = 2 * kBlock * HD;   // elements of one head's K and V of a block
+  const uint16_t* pool = kv + ((size_t)layer * NB * n_kv + kvh) * HS;
   // The block ids live in LDS for the whole item: a K/V address then never
   // waits on a global load, which (vector loads complete in order) would also
   // wait for every tile already in flight.
   {
     const int* bt = bt_store + it.bt_off;
     const int nblk = (kmax + kBlock - 1) / kBlock;
-    for (int i = threadIdx.x; i < nblk; i += 256) sbt[i] = bt[i];
+    for (int i = threadIdx.x; i < nblk; i += 256) sbt[i] = bt[i] * n_kv;   // in units of HS
     __syncthreads();
   }
 
@@ -1382,31 +1404,41 @@ __global__ __launch_bounds__(256, PREFILL_WPE) void k_prefill_attn(const Prefill
   }
   const int qpos = it.pos0 + 32 * w + c32;   // this lane's query position
 
-  // Tile t of K and V, both by direct loads into their rings (slot t % NKS).
+  // Tiles of K and V go by direct loads into their rings (tile t in slot t % NKS).
   // K fragment s holds key t*32 + l%32, dims 16s + 8(l/32) .. +8 in lane l.
   // V keeps its natural [key][dim] rows; the 16-byte chunk c of row r sits at
   // chunk position c ^ 2(r % 4), so the four rows a transposed read touches
-  // fall on different LDS banks.
+  // fall on different LDS banks. The block ids of the next loads (kid, vid) are
+  // read an iteration before their addresses are formed. The eight rows of V that
+  // a wave brings lie in one block (rows past kmax - 1 repeat that one, which is
+  // then among them or all of them).
   const int vrow_in = lane / CPR, vcp = lane % CPR;
-  auto issue_kv = [&](int t) {
-    {
-      const int key = min(t * TK + c32, kmax - 1);
-      const uint16_t* base = pool + (size_t)sbt[key >> 4] * bstride + (key & 15) * HD + 8 * hf;
-      unsigned char* sl = sKd + (t % NKS) * KFR * 1024;
+  auto k_key = [&](int t) { return min(t * TK + c32, kmax - 1); };
+  auto v_key = [&](int t, int i) { return min(t * TK + (w * VPW + i) * KPF + vrow_in, kmax - 1); };
+  static_assert(VPW * KPF == 8, "V rows per wave");
+  unsigned kid, vid;
+  auto ids = [&](int tk, int tv) {
+    kid = sbt[k_key(tk) >> 4];
+    vid = sbt[min(tv * TK + 8 * w, kmax - 1) >> 4];
+  };
+  auto issue_k = [&](int t) {
+    const uint16_t* base = pool + (size_t)kid * HS + (k_key(t) & 15) * HD + 8 * hf;
+    unsigned char* sl = sKd + (t % NKS) * KFR * 1024;
 #pragma unroll
-      for (int i = 0; i < KPW; ++i) {
-        const int s = w * KPW + i;
-        __builtin_amdgcn_global_load_lds((const void*)(base + 16 * s), MOA_LDS(sl + s * 1024), 16, 0, 0);
-      }
+    for (int i = 0; i < KPW; ++i) {
+      const int s = w * KPW + i;
+      __builtin_amdgcn_global_load_lds((const void*)(base + 16 * s), MOA_LDS(sl + s * 1024), 16, 0, 0);
     }
+  };
+  auto issue_v = [&](int t) {
     unsigned char* vs = sV + (t % NKS) * VFR * 1024;
+    const uint16_t* base = pool + (size_t)(unsigned)__builtin_amdgcn_readfirstlane(vid) * HS + kBlock * HD;
 #pragma unroll
     for (int i = 0; i < VPW; ++i) {
       const int f = w * VPW + i;
       const int r = f * KPF + vrow_in;                    // row of the tile this lane fills
-      const int key = min(t * TK + r, kmax - 1);
       const int gc = vcp ^ ((r & 3) << 1);                // chunk of the key's row it brings
-      const uint16_t* src = pool + (size_t)sbt[key >> 4] * bstride + kBlock * HD + (key & 15) * HD + gc * 8;
+      const uint16_t* src = base + (unsigned)((v_key(t, i) & 15) * HD + gc * 8);
       __builtin_amdgcn_global_load_lds((const void*)src, MOA_LDS(vs + f * 1024), 16, 0, 0);
     }
   };
@@ -1430,64 +1462,126 @@ __global__ __launch_bounds__(256, PREFILL_WPE) void k_prefill_attn(const Prefill
   f32x16_t O[DT];
 #pragma unroll
   for (int d = 0; d < DT; ++d) O[d] = f32x16_t{};
-  float m = -INFINITY, l = 0.f;
+  float l = 0.f;
 
-  // Every iteration issues the same loads, past the last tile too (keys are
-  // clamped to kmax - 1, so those read valid memory and land in slots nobody
-  // reads): the number of loads in flight is then the same at every point of
-  // the loop, and each wait below is exact rather than a full drain.
-  issue_kv(0);
-  issue_kv(1);
-  for (int t = 0; t < ntile; ++t) {
-    // tile t landed (loads issued after it: tile t+1's)
-    wait_vmcnt<KPW + VPW>();
-    barrier();                               // tile t visible; slots of t-1 free
-    issue_kv(t + 2);
-    const unsigned char* sl = (sKd + (t % NKS) * KFR * 1024) + lane * 16;
-    // two independent accumulation chains (q hi, q lo) keep the MFMA pipe busy
-    f32x16_t S = f32x16_t{}, S2 = f32x16_t{};
-#pragma unroll
-    for (int s = 0; s < DS; ++s) {
-      const u32x4 ka = *(const u32x4*)(sl + s * 1024);
-      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, qh[s]), S, 0, 0, 0);
-      S2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, ql[s]), S2, 0, 0, 0);
-    }
-    S += S2;
-    // causal mask (only tiles that reach past the wave's first query or past
-    // kmax need it) and online softmax for query qpos (element e: key kb +
-    // 8(e/4) + e%4)
+  // One 16-dim step of a tile's scores. The accumulator starts from the row's
+  // negated reference maximum, so the scores come out relative to it.
+  f32x16_t A, nm = f32x16_t{};               // nm: the row's -reference, sixteen times
+  auto kfrag = [&](int t, int s) { return *(const u32x4*)(sKd + ((t % NKS) * KFR + s) * 1024 + lane * 16); };
+  auto score = [&](int s, const u32x4& ka) {
+    A = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, qh[s]), s ? A : nm, 0, 0, 0);
+    A = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, ql[s]), A, 0, 0, 0);
+  };
+  // causal mask (only tiles that reach past the wave's first query or past
+  // kmax need it) for query qpos (element e: key kb + 8(e/4) + e%4)
+  auto mask = [&](int t, f32x16_t& A) {
     const int kb = t * TK + 4 * hf;
     if (t * TK + TK - 1 > it.pos0 + 32 * w || t * TK + TK > kmax) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int key = kb + 8 * (e >> 2) + (e & 3);
-        if (key > qpos || key >= kmax) S[e] = -INFINITY;
+        if (key > qpos || key >= kmax) A[e] = -INFINITY;
       }
     }
+  };
+  // Every iteration issues the same loads, past the last tile too (keys are
+  // clamped to kmax - 1, so those read valid memory and land in slots nobody
+  // reads): the number of loads in flight is then the same at every point of
+  // the loop, and each wait below is exact rather than a full drain. Iteration t
+  // multiplies K of tile t + 1 and V of tile t, so K is issued three tiles
+  // ahead and V two, each into the slot that iteration t - 1 read.
+  ids(0, 0);
+  issue_k(0);
+  ids(1, 0);
+  issue_k(1);
+  issue_v(0);
+  ids(2, 1);
+  issue_k(2);
+  issue_v(1);
+  ids(3, 2);
+  wait_vmcnt<2 * (KPW + VPW)>();
+  barrier();
+#pragma unroll
+  for (int s = 0; s < DS; ++s) score(s, kfrag(0, s));
+  f32x16_t S = A;
+  mask(0, S);
+  auto row_max = [&] {
     float mx = S[0];
 #pragma unroll
     for (int e = 1; e < 16; ++e) mx = fmaxf(mx, S[e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    // The reference maximum moves only when a score exceeds it by more than
-    // 2^8 (log2 units): probabilities then stay below 256, exact in the split
-    // and harmless in fp32, and the rescale of O below is rare.
-    const float mn = (mx > m + 8.f) ? mx : m;
-    const float base = (mn == -INFINITY) ? 0.f : mn;   // a row with no key yet keeps m = -inf
-    const float alpha = __builtin_amdgcn_exp2f(m - base);
-    float ts = 0.f;
+    return max_halves(mx);
+  };
+  {                                          // the first reference: every row may see key 0
+    const float mx = row_max();
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      S[e] = __builtin_amdgcn_exp2f(S[e] - base);
-      ts += S[e];
+      nm[e] = -mx;
+      S[e] -= mx;
     }
-    ts += __shfl_xor(ts, 32, 64);
-    l = l * alpha + ts;
-    m = mn;
-    if (!__all(alpha == 1.f)) {                // no row's maximum moved: nothing to rescale
+  }
+  auto step = [&](int t, auto more) {
+    // K of tile t + 1 and V of tile t landed (issued after them: K t+2, V t+1)
+    wait_vmcnt<KPW + VPW>();
+    barrier();                               // visible; the slots of iteration t - 1 are free
+    // The next tile's scores beside this tile's softmax, two MFMAs and a share of
+    // the softmax at a time: the matrix cores work while the VALU does, in one wave.
+    float ts = 0.f;
+    u32x4 ph[2], pl[2];                        // P as the B operand: slot j of 16-key step u is key 16u + 8(j/4) + 4(l/32) + j%4
+    // The reference moves only when a score exceeds it by more than 2^8 (log2
+    // units): probabilities then stay below 256, exact in the split and
+    // harmless in fp32, and correcting what is relative to it is rare.
+    auto reference = [&] {
+      const float mx = row_max();
+      if (__all(mx <= 8.f)) return;
+      const float up = mx > 8.f ? mx : 0.f, alpha = __builtin_amdgcn_exp2f(-up);
+      l *= alpha;
 #pragma unroll
       for (int d = 0; d < DT; ++d) O[d] *= alpha;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        S[e] -= up;
+        nm[e] -= up;
+        if constexpr (more.value) A[e] -= up;
+      }
+    };
+    auto split = [&](int j) {
+      unsigned hv, lv;
+      split_pair(S[2 * j], S[2 * j + 1], hv, lv);
+      asm volatile("" : "+v"(hv), "+v"(lv));   // here and not beside their use
+      ph[j >> 2][j & 3] = hv;
+      pl[j >> 2][j & 3] = lv;
+    };
+    auto pair = [&](int j) {
+#pragma unroll
+      for (int e = 2 * j; e < 2 * j + 2; ++e) {
+        S[e] = __builtin_amdgcn_exp2f(S[e]);
+        ts += S[e];
+      }
+      asm volatile("" : "+v"(ts));
+      if (j < 4) split(j);                     // the others beside the first half of P V
+    };
+    if constexpr (more.value) {
+      u32x4 kf[3] = {kfrag(t + 1, 0), kfrag(t + 1, 1), u32x4{}};
+#pragma unroll
+      for (int s = 0; s < DS; ++s) {
+        if (s + 2 < DS) kf[(s + 2) % 3] = kfrag(t + 1, s + 2);
+        score(s, kf[s % 3]);
+        if (s == 1) issue_k(t + 3);
+        if (s == 2) issue_v(t + 2);
+        if (s == 3) ids(t + 4, t + 3);
+        if (s == 0) reference();
+        else
+#pragma unroll
+          for (int j = (s - 1) * 8 / (DS - 1); j < s * 8 / (DS - 1); ++j) pair(j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      reference();
+#pragma unroll
+      for (int j = 0; j < 8; ++j) pair(j);
     }
-    // O^T += V^T P^T over two 16-key steps; slot j of step u is key 16u + 8(j/4) + 4(l/32) + j%4
+    l += ts;                                   // of this half-wave's keys
+    // O^T += V^T P^T over two 16-key steps.
     // The V reads are explicit LDS instructions with an explicit wait tied to
     // their registers: the compiler, which cannot tell them from the ring
     // slots the direct loads are filling, would otherwise wait for every load
@@ -1505,17 +1599,26 @@ __global__ __launch_bounds__(256, PREFILL_WPE) void k_prefill_attn(const Prefill
       for (int d = 0; d < DT; ++d) lgkm_wait_for(va[u][d]);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      unsigned ph[4], pl[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) split_pair(S[8 * u + 2 * j], S[8 * u + 2 * j + 1], ph[j], pl[j]);
-      const u32x4 pa = u32x4{ph[0], ph[1], ph[2], ph[3]}, pb = u32x4{pl[0], pl[1], pl[2], pl[3]};
+      for (int d = 0; d < DT; ++d)
+        O[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, va[u][d]), __builtin_bit_cast(bf16x8_t, ph[u]), O[d], 0, 0, 0);
 #pragma unroll
       for (int d = 0; d < DT; ++d) {
-        O[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, va[u][d]), __builtin_bit_cast(bf16x8_t, pa), O[d], 0, 0, 0);
-        O[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, va[u][d]), __builtin_bit_cast(bf16x8_t, pb), O[d], 0, 0, 0);
+        O[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, va[u][d]), __builtin_bit_cast(bf16x8_t, pl[u]), O[d], 0, 0, 0);
+        if (u == 0)
+#pragma unroll
+          for (int j = 4 + d * 4 / DT; j < 4 + (d + 1) * 4 / DT; ++j) split(j);
       }
+      if (u == 0) __builtin_amdgcn_sched_barrier(0);
     }
-  }
+    if constexpr (more.value) {
+      S = A;
+      mask(t + 1, S);
+    }
+  };
+  for (int t = 0; t + 1 < ntile; ++t) step(t, std::true_type{});
+  step(ntile - 1, std::false_type{});
+  l = add_halves(l);
   wait_vmcnt<0>();                           // no load may land in LDS after this workgroup ends
   // normalise and store: element e of O[d] is dim 32d + 8(e/4) + 4(l/32) + e%4 of row 32w + l%32
   const int r = 32 * w + c32;

@@ -139,3 +139,26 @@ def test_bf16_row_gemms(rows, d, ffn, nh, nkv, hd):
     for i, (p, m, _) in enumerate(reqs):
         compare(shape, ws[m], p, toks[i], logs[i], True, 2e-2, what=f"{rows} call {i}", report_pure=False)
         assert np.array_equal(toks[i], one[i]) and np.array_equal(logs[i], logs1[i])
+
+
+# prefill attention: key tiles of 32 and row tiles of 32 and 128 with their edges, one tile alone, both head widths, chunks
+# of 96 rows that begin inside a tile's block; with W_q times 32 the scores spread over tens of log2 units, so that rows'
+# reference maxima move in later tiles and probabilities reach 2^8
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("lens", [(1, 31, 32, 33), (63, 64, 65, 97), (127, 128, 129, 161), (300,)])
+@pytest.mark.parametrize("sharp", [False, True])
+def test_prefill_attention_tiles(hd, lens, sharp):
+    shape = ModelShape(n_layers=1, d_model=512, n_heads=4, n_kv_heads=2, head_dim=hd, ffn_dim=256, vocab=512)
+    w = generate_weights(shape, "bf16", 11, 97, 0)
+    if sharp:
+        q = [n for n in w if n.endswith("wq")]
+        assert len(q) == 1
+        w[q[0]] = np.where(w[q[0]] & 0x7f80, w[q[0]] + np.uint16(5 << 7), w[q[0]]).astype(np.uint16)
+    for budget in (96, 512):
+        consts = EngineConsts(num_kv_blocks=128, max_num_seqs=8, max_prefill_tokens=budget, max_model_len=512)
+        rng = np.random.default_rng(list(lens))
+        reqs = [(rng.integers(0, shape.vocab, n).astype(np.int32), 0, 2) for n in lens]
+        toks, logs = run_requests(shape, "bf16", consts, [w], reqs)
+        for i, (p, _, _) in enumerate(reqs):
+            compare(shape, w, p, toks[i], logs[i], True, 2e-2, what=f"{len(p)} tokens, budget {budget}",
+                    report_pure=False)
