@@ -286,8 +286,8 @@ enum {
   MOA_K_GEMM_O, MOA_K_GEMM_GATEUP, MOA_K_GEMM_DOWN, MOA_K_GEMM_LMHEAD, MOA_K_ARGMAX, MOA_K_PREFILL_ATTN,
   /* Two views of the GEMM launches above, by the kernel that runs them: every
    * qkv / o / gate-up / down / LM-head launch is counted once more in exactly
-   * one of these (the workgroup-tile kernel of small and medium row counts,
-   * or the 128-row-tile matrix-core kernel of large row counts). A sum over
+   * one of these (the kernels of small and medium row counts, or the
+   * 128-row-tile matrix-core kernel of large row counts). A sum over
    * classes must leave them out. */
   MOA_K_GEMM_SMALL_M, MOA_K_GEMM_LARGE_M,
   MOA_K_COUNT
