@@ -1327,19 +1327,18 @@ __device__ __forceinline__ float add_halves(float x) {
 // q and P enter the MFMAs as split bf16 (hi + lo, two MFMAs each). K and V tiles
 // reach LDS by direct global->LDS loads into three-stage rings, K in MFMA fragment
 // order, V in its rows, read transposed.
-// Bound by issue: per tile a wave owes 32 MFMAs and ~160 VALU instructions, and
-// the SIMD's two waves together keep the matrix cores 58% and the VALU 48% busy.
+// Bound by issue: per tile a wave owes 32 MFMAs and ~190 VALU instructions, and
+// the SIMD's two waves together keep the matrix cores 58% and the VALU 55% busy.
 // So both are kept short and side by side:
 //  * the next tile's scores are multiplied between this tile's softmax
 //    instructions, two MFMAs and a share of the softmax at a time, and half of P
 //    is split between the MFMAs of P V;
-//  * the scores' accumulator starts from minus the reference maximum, which saves
-//    the subtraction, and q hi and q lo share one chain, which saves an addition;
 //  * addresses: wave-uniform parts are scalar, block ids are read an iteration
 //    ahead in units of one head's block.
 // Mean launch over 9,001- and 17,003-token prompts at 32 heads of 128 (16k-row
-// chunks): 3,155 us with scores, softmax and P V one after the other, 2,995 with them
-// side by side, 2,759 with the VALU instructions per MFMA cut from 6.7 to 5.0.
+// chunks): 3,281 us with scores, softmax and P V one after the other, 2,878 so.
+// Starting the scores' sums from minus the reference maximum and running q hi and
+// q lo in one chain would save 37 us more, but loses precision (see below).
 #ifndef PREFILL_WPE
 #define PREFILL_WPE 2
 #endif
@@ -1462,25 +1461,26 @@ __global__ __launch_bounds__(256, PREFILL_WPE) void k_prefill_attn(const Prefill
   f32x16_t O[DT];
 #pragma unroll
   for (int d = 0; d < DT; ++d) O[d] = f32x16_t{};
-  float l = 0.f;
+  float m = -INFINITY, l = 0.f;
 
-  // One 16-dim step of a tile's scores. The accumulator starts from the row's
-  // negated reference maximum, so the scores come out relative to it.
-  f32x16_t A, nm = f32x16_t{};               // nm: the row's -reference, sixteen times
+  // One 16-dim step of a tile's scores, in two chains that both grow from zero:
+  // a sum that starts at the reference maximum rounds every product at that
+  // magnitude, the small q lo ones too (2.6x the rounding error at head_dim 128).
+  f32x16_t A, A2;                            // q hi, q lo
   auto kfrag = [&](int t, int s) { return *(const u32x4*)(sKd + ((t % NKS) * KFR + s) * 1024 + lane * 16); };
   auto score = [&](int s, const u32x4& ka) {
-    A = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, qh[s]), s ? A : nm, 0, 0, 0);
-    A = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, ql[s]), A, 0, 0, 0);
+    A = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, qh[s]), s ? A : f32x16_t{}, 0, 0, 0);
+    A2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ka), __builtin_bit_cast(bf16x8_t, ql[s]), s ? A2 : f32x16_t{}, 0, 0, 0);
   };
   // causal mask (only tiles that reach past the wave's first query or past
   // kmax need it) for query qpos (element e: key kb + 8(e/4) + e%4)
-  auto mask = [&](int t, f32x16_t& A) {
+  auto mask = [&](int t, f32x16_t& S) {
     const int kb = t * TK + 4 * hf;
     if (t * TK + TK - 1 > it.pos0 + 32 * w || t * TK + TK > kmax) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int key = kb + 8 * (e >> 2) + (e & 3);
-        if (key > qpos || key >= kmax) A[e] = -INFINITY;
+        if (key > qpos || key >= kmax) S[e] = -INFINITY;
       }
     }
   };
@@ -1503,45 +1503,31 @@ __global__ __launch_bounds__(256, PREFILL_WPE) void k_prefill_attn(const Prefill
   barrier();
 #pragma unroll
   for (int s = 0; s < DS; ++s) score(s, kfrag(0, s));
-  f32x16_t S = A;
+  f32x16_t S = A + A2;
   mask(0, S);
-  auto row_max = [&] {
-    float mx = S[0];
-#pragma unroll
-    for (int e = 1; e < 16; ++e) mx = fmaxf(mx, S[e]);
-    return max_halves(mx);
-  };
-  {                                          // the first reference: every row may see key 0
-    const float mx = row_max();
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      nm[e] = -mx;
-      S[e] -= mx;
-    }
-  }
   auto step = [&](int t, auto more) {
     // K of tile t + 1 and V of tile t landed (issued after them: K t+2, V t+1)
     wait_vmcnt<KPW + VPW>();
     barrier();                               // visible; the slots of iteration t - 1 are free
     // The next tile's scores beside this tile's softmax, two MFMAs and a share of
     // the softmax at a time: the matrix cores work while the VALU does, in one wave.
-    float ts = 0.f;
+    float ts = 0.f, base, alpha;
     u32x4 ph[2], pl[2];                        // P as the B operand: slot j of 16-key step u is key 16u + 8(j/4) + 4(l/32) + j%4
-    // The reference moves only when a score exceeds it by more than 2^8 (log2
-    // units): probabilities then stay below 256, exact in the split and
-    // harmless in fp32, and correcting what is relative to it is rare.
+    // The reference maximum moves only when a score exceeds it by more than
+    // 2^8 (log2 units): probabilities then stay below 256, exact in the split
+    // and harmless in fp32, and the rescale of O below is rare.
     auto reference = [&] {
-      const float mx = row_max();
-      if (__all(mx <= 8.f)) return;
-      const float up = mx > 8.f ? mx : 0.f, alpha = __builtin_amdgcn_exp2f(-up);
-      l *= alpha;
+      float mx = S[0];
 #pragma unroll
-      for (int d = 0; d < DT; ++d) O[d] *= alpha;
+      for (int e = 1; e < 16; ++e) mx = fmaxf(mx, S[e]);
+      mx = max_halves(mx);
+      const float mn = (mx > m + 8.f) ? mx : m;
+      base = (mn == -INFINITY) ? 0.f : mn;     // a row with no score yet keeps m = -inf
+      alpha = __builtin_amdgcn_exp2f(m - base);
+      m = mn;
+      if (!__all(alpha == 1.f)) {              // no row's maximum moved: nothing to rescale
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        S[e] -= up;
-        nm[e] -= up;
-        if constexpr (more.value) A[e] -= up;
+        for (int d = 0; d < DT; ++d) O[d] *= alpha;
       }
     };
     auto split = [&](int j) {
@@ -1554,7 +1540,7 @@ __global__ __launch_bounds__(256, PREFILL_WPE) void k_prefill_attn(const Prefill
     auto pair = [&](int j) {
 #pragma unroll
       for (int e = 2 * j; e < 2 * j + 2; ++e) {
-        S[e] = __builtin_amdgcn_exp2f(S[e]);
+        S[e] = __builtin_amdgcn_exp2f(S[e] - base);
         ts += S[e];
       }
       asm volatile("" : "+v"(ts));
@@ -1580,7 +1566,7 @@ __global__ __launch_bounds__(256, PREFILL_WPE) void k_prefill_attn(const Prefill
 #pragma unroll
       for (int j = 0; j < 8; ++j) pair(j);
     }
-    l += ts;                                   // of this half-wave's keys
+    l = l * alpha + add_halves(ts);
     // O^T += V^T P^T over two 16-key steps.
     // The V reads are explicit LDS instructions with an explicit wait tied to
     // their registers: the compiler, which cannot tell them from the ring
@@ -1612,13 +1598,12 @@ __global__ __launch_bounds__(256, PREFILL_WPE) void k_prefill_attn(const Prefill
       if (u == 0) __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (more.value) {
-      S = A;
+      S = A + A2;
       mask(t + 1, S);
     }
   };
   for (int t = 0; t + 1 < ntile; ++t) step(t, std::true_type{});
   step(ntile - 1, std::false_type{});
-  l = add_halves(l);
   wait_vmcnt<0>();                           // no load may land in LDS after this workgroup ends
   // normalise and store: element e of O[d] is dim 32d + 8(e/4) + 4(l/32) + e%4 of row 32w + l%32
   const int r = 32 * w + c32;
