@@ -426,6 +426,26 @@ bool step_is_timed(const moa_engine* e, bool noalloc) {
   return !noalloc && e->time_every > 0 && (e->step_idx % e->time_every) == 0;
 }
 
+// k-split of the small-M kernel: powers of two until the launch would keep
+// `target` workgroups of 16..64 rows x 128 (256 past 64 rows) columns in flight.
+// From weight-streaming sweeps with cold weights: deep-K projections (K >= 4N)
+// stream best with half the workgroups (longer k runs), square ones at up to 8
+// rows with twice as many (k runs of 4 steps). The consumer adds the partial
+// sums in order, so S is also what fixes the step's last bits.
+int small_split(const moa_engine* e, const GemmPlanIn& in, int maxM, int totalM, int K, int N) {
+  const int KS = K / 32;
+  const int rows_per = maxM <= 16 ? 16 : (maxM <= 32 ? 32 : 64);
+  const int tiles = N / ((maxM > 64 && N % 256 == 0) ? 256 : 128);
+  int target = 1024, kmul = 8, base = 0;
+  for (int g = 0; g < in.ngroups; ++g) base += ((in.nrows[g] + rows_per - 1) / rows_per) * tiles;
+  if (K >= 4 * N) target /= 2;
+  else if (K == N && maxM <= 8) { target *= 2; kmul = 4; }
+  int S = 1;
+  while (base * S < target && KS % (S * 2 * kmul) == 0 && (int64_t)S * 2 * totalM * N <= e->lay.part_cap && S < 16)
+    S *= 2;
+  return S;
+}
+
 void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K, int N, int epi, const void* X,
                size_t x_lo, float* out, uint16_t* hout, size_t h_lo, bool allow_split, GemmArgs& a, int& mt,
                int& nt, bool& large) {
@@ -617,35 +637,19 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
       return;
     }
   }
-  // Small-M kernel: items of 16*wmt rows x 64*wnt columns (every bf16
-  // projection width is a multiple of 128: moa_create checks it). Up to 8 rows
-  // it packs both activation planes into one MFMA (wmt 1, wnt 2) on workgroups
-  // of 32 columns; else on workgroups of 64.
-  const int wmt = maxM <= 8 ? 1 : (maxM <= 16 && N % 256 == 0 ? 1 : (maxM <= 32 ? 2 : 4));
-  const int wnt = (wmt == 1 && maxM > 8) ? 4 : 2;
-  mt = kWgTile + wmt;
-  nt = wnt;
-  const int tiles = N / (64 * wnt);
+  // Small-M kernel: items of 16, 32 or 64 rows x 128 columns (every bf16
+  // projection width is a multiple of 128: moa_create checks it), 64 where that
+  // leaves CUs idle, 32 for F32 outputs where it leaves half of them idle. us per
+  // step of four 1B layers at 16 rows: 258, with half these thresholds 273, with
+  // twice them 272
+  const int wmt = maxM <= 16 ? 1 : (maxM <= 32 ? 2 : 4);
   const int rows_per = 16 * wmt;
-  int base = 0, chunks = 0;
+  const int S = allow_split ? small_split(e, in, maxM, totalM, K, N) : 1;
+  int chunks = 0;
   for (int g = 0; g < in.ngroups; ++g) chunks += (in.nrows[g] + rows_per - 1) / rows_per;
-  base = chunks * (N / (maxM <= 8 ? 32 : 64));       // workgroups per k-split
-  // k-split: 4, which with the waves' own split puts all of a qkv or O matrix in
-  // flight at once; 2 for a long K (from 12,288: a wave still has 48 k-steps),
-  // 8 where 4 leaves CUs idle. At least 4 k-steps per wave up to 8 rows, 2 above.
-  // Swept at 1, 8, 16, 32 and 64 rows on one and three models of both widths:
-  // within 5% of the best power of two but for 8B qkv at 16 rows (12.9 us, 11.6 at 8).
-  // Above 16 rows ~192 workgroups (1B o, qkv at 24 to 128 rows: the best of 1..16).
-  int S = 1;
-  if (allow_split) {
-    int want = maxM <= 8 ? (KS >= 384 ? 2 : 4) : (base * 4 < 256 ? 8 : 4);
-    if (maxM > 16)                                   // ~192 workgroups of 64 columns
-      for (want = 1; want < 8 && base * want < 192;) want *= 2;
-    const int min_k = maxM <= 8 ? 4 : 2;
-    while (S < want && KS % (S * 2 * 4) == 0 && KS / (S * 2 * 4) >= min_k &&
-           (int64_t)S * 2 * totalM * N <= e->lay.part_cap)
-      S *= 2;
-  }
+  mt = kWgTile + wmt;
+  const int items = chunks * S * (N / 128);
+  nt = items >= 256 ? 8 : (items >= 128 || epi != EPI_F32 ? 4 : 2);
   a.S = S;
   a.ksteps = KS / S;
   a.out_split = (size_t)totalM * N;  // partial s lives at out + s * rows * N
@@ -655,7 +659,7 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
     a.g[k].W = in.W[g]; a.g[k].row0 = in.row0[g]; a.g[k].nrows = in.nrows[g];
     a.g[k].n_mc = (in.nrows[g] + rows_per - 1) / rows_per;
     a.g[k].item0 = item;
-    item += a.g[k].n_mc * S * tiles;
+    item += a.g[k].n_mc * S * (N / (16 * nt));
   }
   a.total_items = item;
 }

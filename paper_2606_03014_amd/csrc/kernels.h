@@ -43,9 +43,9 @@ struct GemmArgs {
 enum Epilogue { EPI_F32 = 0, EPI_SWIGLU = 1 };
 
 // launch_gemm(mt = kWgTile + MT, nt): the small-M kernel; each item is 16*MT
-// rows x 64*nt columns x one of S k-splits of ksteps k-steps (ksteps % 4 == 0,
-// S * ksteps == K / 32, N % (64*nt) == 0). MT = 1 with nt = 2: groups of at most
-// 8 rows; MT = 1 with nt = 4, MT = 2 or 4 with nt = 2: 16*MT rows per chunk.
+// rows (MT = 1, 2 or 4) x 16*nt columns (nt = 8 or 4; 2 too with EPI_F32) x one of
+// S k-splits of ksteps k-steps (ksteps % 4 == 0, S * ksteps == K / 32,
+// N % (16*nt) == 0).
 constexpr int kWgTile = 1000;
 // launch_gemm(mt = kMmTile + RT, nt): the medium-M kernel; each item is 16*RT
 // rows (RT = 2, 4 or 8) x NW*CT*16 columns x one of S k-splits of K/32/S

@@ -102,6 +102,13 @@ __device__ __forceinline__ void store_split(uint16_t* p, size_t lo, size_t i, fl
   p[i + lo] = f2bf(v - bf2f(h));
 }
 
+// silu(gate) * up, rounded once more before it is split: without the pragma one
+// kernel would fuse the product into the split's subtraction and another not.
+__device__ __forceinline__ float silu_mul(float g, float up) {
+#pragma clang fp contract(off)
+  return g / (1.f + __expf(-g)) * up;
+}
+
 // Order this wavefront's LDS writes before its later LDS reads (no workgroup barrier).
 __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -288,132 +295,149 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(float* __restrict__ x, con
 // B = column l%16, same k; D = column l%16, rows 4*(l/16)..+4.
 //
 // ------------------------------------------ bf16 GEMM, small row counts
-// Up to 16 rows per model (and, at 64 rows per chunk, the widths and grids the
-// medium-M kernel below does not take): the launch is a stream of weights that
-// nothing but latency should slow down.
-//  * A workgroup owns 16 * MT rows x 16 * CT columns of one k-split, and its
-//    four waves a quarter of that split's k each; their sums meet in LDS in
-//    fixed order. Splitting k inside the workgroup is what lets a wave own so
-//    few columns: enough workgroups to keep every CU's loads in flight, without
-//    the partial sums of as many k-splits (4 instead of 16, which the next
-//    kernel would read back).
-//  * No LDS staging and no barrier in the k loop: weights and activation
-//    fragments go straight to registers, D k-steps ahead, the same loads every
-//    step (clamped to the last), so the waits stay exact. The activations come
-//    from L2; weights are read once and loaded non-temporally (4-8% faster).
-//  * PACK (at most 8 rows): rows 0-7 of the MFMA's A operand are the hi plane,
-//    rows 8-15 the lo plane of the same rows, so one MFMA and one 1 KB activation
-//    read per weight fragment do the work of two; the halves are added at the end.
+// Up to 16 rows per model (and, at up to 64 rows per chunk, the widths and grids
+// the medium-M kernel below does not take): the launch is a stream of weights
+// that nothing but latency should slow down.
+//  * A workgroup owns 16 * MT rows x 16 * NW * CT columns of one k-split, each of its
+//    NW waves CT column tiles, and runs the split's k-steps in order, hi plane
+//    before lo: one chain per output and split, so the sums are those of any
+//    other kernel on the same split, bit for bit.
+//  * Weights go straight to registers, R stages of four k-steps ahead, the same
+//    loads every stage (clamped to the last), so the waits stay exact. A chain over
+//    all of K (gate-up, LM head) has few waves, so each keeps up to 32 KB in flight.
+//  * The activations (both planes, in MFMA A order) pass through registers into a
+//    two-slot LDS ring that the waves share: loaded as far ahead as the weights
+//    (vector loads complete in order, so waiting for a younger load waits for every
+//    older one), written a stage ahead, one barrier per stage that leaves them in flight.
 //  * Workgroup ids are remapped so that each XCD streams one contiguous range
-//    of columns (8B gate-up at 1 row: 44.5 -> 38.4 us against the plain order) and
-//    row chunks sharing weights run side by side on it.
-// Cold weights, us per launch, before (LDS-staged workgroup tiles with up to 16
-// k-splits) -> now: 8B gate-up 47.9 -> 38.4 at 1 row, 50.0 -> 42.2 at 16; 8B down
-// 24.5 -> 19.8, 25.7 -> 22.5; 8B qkv 10.8 -> 9.7, 11.8 -> 12.9 (its four partials
-// instead of 16 save more than that in the RoPE launch); 1B gate-up 23.7 -> 12.6,
-// 25.4 -> 13.5; 1B gate-up at 64 rows 42 -> 25; three 8B models at 1 row: gate-up
-// 125 -> 106, down 61 -> 53, qkv 29.6 -> 24.3.
+//    of columns, and row chunks sharing weights run side by side on it.
+// us per launch, 128-column workgroups with the next stage's loads issued together
+// and copied -> this: 8B gate-up 50.4 -> 37.8 at 8 rows, 52.8 -> 39.8 at 16 (6.2 and
+// 5.9 TB/s); o and down (mean) 23.7 -> 19.6, 25.0 -> 20.4; qkv 12.0 -> 12.3, 12.6 ->
+// 13.3; a head of 4,096 40.8 -> 16.0. 1B gate-up 23.9 -> 14.1, 25.2 -> 14.6; o and
+// down 12.1 -> 7.6, 12.8 -> 8.4; qkv 5.2 -> 5.7; head 20.6 -> 10.1. Measured and not
+// kept: four stages ahead (1B gate-up 17.8), activations from L2 straight to
+// registers (level up to 8 rows, 10-20% slower steps at 16), sums of four waves'
+// quarters of a split (up to 10% faster, but another order: other last bits).
 __device__ __forceinline__ u32x4 load_stream(const u32x4* p) { return __builtin_nontemporal_load(p); }
 
-template <int MT, int CT, int D, int EPI, bool PACK, int WPE>
-__global__ __launch_bounds__(256, WPE) void k_gemm_sm(GemmArgs a, int nblk, int item_cols) {
-  constexpr int AP = PACK ? 1 : 2 * MT;              // activation fragments per k-step
-  __shared__ float red[4][MT * CT][256];
+template <int MT, int CT, int NW, int R, int EPI>
+__global__ __launch_bounds__(64 * NW, 2) void k_gemm_sm(GemmArgs a, int nblk) {
+  constexpr int UK = 4;                              // k-steps per stage
+  constexpr int PER = 2 * MT * UK / NW;              // activation fragments per wave and stage
+  __shared__ __align__(16) unsigned char sA[2][2 * MT * UK * 1024];
   const int per = (nblk + 7) / 8;
   const int blk = (blockIdx.x % 8) * per + blockIdx.x / 8;
   if (blk >= nblk) return;
-  const int sub = item_cols / (16 * CT);             // workgroups per item
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const void* Wg = a.g[0].W;
   int row0 = a.g[0].row0, nrows = a.g[0].nrows, n_mc = a.g[0].n_mc, item0 = a.g[0].item0;
 #pragma unroll
   for (int i = 1; i < kMaxGroups; ++i) {
-    if (i < a.ngroups && a.g[i].item0 * sub <= blk) {
+    if (i < a.ngroups && a.g[i].item0 <= blk) {
       Wg = a.g[i].W; row0 = a.g[i].row0; nrows = a.g[i].nrows; n_mc = a.g[i].n_mc; item0 = a.g[i].item0;
     }
   }
-  // a group's workgroups: ((column block, split), column sub-block), row chunk fastest
-  int idx = blk - item0 * sub;
+  // a group's workgroups: (column block, split), row chunk fastest
+  const int idx = blk - item0;
   const int mc = idx % n_mc;
-  idx /= n_mc;
-  const int sb = idx % sub;
-  idx /= sub;
-  const int s = idx % a.S, nb = idx / a.S;
-  const int tile0 = (nb * sub + sb) * CT;            // first 16-column tile
-  const int KS = a.K >> 5;
-  const int k0 = (w * a.ksteps) >> 2, nk = (((w + 1) * a.ksteps) >> 2) - k0;   // >= 1: ksteps % 4 == 0
-  const int ks0 = s * a.ksteps + k0;
+  const int s = idx / n_mc % a.S, nb = idx / n_mc / a.S;
+  const int tile0 = (nb * NW + w) * CT;              // this wave's first 16-column tile
+  const int KS = a.K >> 5, ns = a.ksteps / UK, ks0 = s * a.ksteps;
   const int rbase = row0 + mc * MT * 16, rend = row0 + nrows;
   const u32x4* bp = (const u32x4*)Wg + ((size_t)tile0 * KS + ks0) * 64 + lane;
   const size_t wt = (size_t)KS * 64;                 // u32x4 between weight tiles
-  const int r16 = lane & 15;
-  const uint16_t* ap[AP];
+  // fragment f of a stage is (plane, row tile, k-step) = (f / (MT * UK), f / UK % MT, f % UK)
+  const uint16_t* ap[PER];
 #pragma unroll
-  for (int m = 0; m < AP; ++m) {
-    const int row = PACK ? min(rbase + (r16 & 7), rend - 1) : min(rbase + 16 * (m >> 1) + r16, rend - 1);
-    const size_t pl = PACK ? (size_t)(r16 >> 3) * a.x_lo : (size_t)(m & 1) * a.x_lo;
-    ap[m] = (const uint16_t*)a.X + pl + (size_t)row * a.K + (size_t)ks0 * 32 + 8 * (lane >> 4);
+  for (int i = 0; i < PER; ++i) {
+    const int f = w * PER + i, pl = f / (MT * UK), m = f / UK % MT, u = f % UK;
+    const int row = min(rbase + 16 * m + (lane & 15), rend - 1);
+    ap[i] = (const uint16_t*)a.X + (size_t)pl * a.x_lo + (size_t)row * a.K + (size_t)(ks0 + u) * 32 + 8 * (lane >> 4);
   }
-  u32x4 b[D][CT], av[D][AP];
-  auto load = [&](int st, int d) {
+  u32x4 ga[R][PER], b[R][UK][CT];
+  auto loadA = [&](int st, int d) {
 #pragma unroll
-    for (int j = 0; j < CT; ++j) b[d][j] = load_stream(bp + j * wt + (size_t)st * 64);
+    for (int i = 0; i < PER; ++i) ga[d][i] = *(const u32x4*)(ap[i] + min(st, ns - 1) * (UK * 32));
+  };
+  auto writeA = [&](int st, int d) {
 #pragma unroll
-    for (int m = 0; m < AP; ++m) av[d][m] = *(const u32x4*)(ap[m] + st * 32);
+    for (int i = 0; i < PER; ++i) *(u32x4*)(sA[st & 1] + (w * PER + i) * 1024 + lane * 16) = ga[d][i];
+  };
+  auto loadB = [&](int st, int d, int u) {
+    const size_t o = (size_t)(min(st, ns - 1) * UK + u) * 64;
+#pragma unroll
+    for (int j = 0; j < CT; ++j) b[d][u][j] = load_stream(bp + j * wt + o);
+  };
+  // LDS only: the loads in flight stay in flight
+  auto barrier = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
   };
   f32x4_t acc[MT][CT];
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
     for (int j = 0; j < CT; ++j) acc[m][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  auto mul = [&](int d) {
+  loadA(0, 0);
 #pragma unroll
-    for (int m = 0; m < AP; ++m)
+  for (int d = 0; d < R; ++d) {
 #pragma unroll
-      for (int j = 0; j < CT; ++j)
-        acc[m / 2][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[d][m]),
-                                                                __builtin_bit_cast(bf16x8_t, b[d][j]), acc[m / 2][j], 0, 0, 0);
-  };
+    for (int u = 0; u < UK; ++u) loadB(d, d, u);
+    if (d + 1 < R) loadA(d + 1, d + 1);
+  }
+  writeA(0, 0);
+  loadA(R, 0);
+  barrier();
+  // Stage st reads slot st & 1 while the other slot takes stage st + 1; the one
+  // barrier per stage makes that slot visible and frees the one just read.
+  for (int st0 = 0; st0 < ns; st0 += R) {
 #pragma unroll
-  for (int d = 0; d < D; ++d) load(min(d, nk - 1), d);
-  int st = 0;
-  for (; st + D < nk; st += D) {
+    for (int d = 0; d < R; ++d) {
+      const int st = st0 + d;
+      if (st >= ns) break;                           // the same for all waves
+      const unsigned char* sl = sA[st & 1] + lane * 16;
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      mul(d);
-      load(min(st + D + d, nk - 1), d);
+      for (int u = 0; u < UK; ++u) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            const u32x4 av = *(const u32x4*)(sl + ((p * MT + m) * UK + u) * 1024);
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+              acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av),
+                                                                  __builtin_bit_cast(bf16x8_t, b[d][u][j]), acc[m][j], 0, 0, 0);
+          }
+        loadB(st + R, d, u);
+        __builtin_amdgcn_sched_barrier(0);           // a fragment's registers are free before they are loaded again
+      }
+      writeA(st + 1, (d + 1) % R);
+      loadA(st + 1 + R, (d + 1) % R);
+      barrier();
     }
   }
-#pragma unroll
-  for (int d = 0; d < D; ++d)
-    if (st + d < nk) mul(d);
   // register i of lane l of a tile is row 4 (l / 16) + i, column l % 16
+  const int col = lane & 15, rq = (lane >> 4) * 4;
 #pragma unroll
-  for (int t = 0; t < MT * CT; ++t)
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) red[w][t][i * 64 + lane] = acc[t / CT][t % CT][i];
-  __syncthreads();
-  constexpr int NT = EPI == EPI_SWIGLU ? MT * CT / 2 : MT * CT;   // output tiles
-  constexpr int PER = PACK ? 128 : 256;                           // outputs of a tile
-  for (int u = threadIdx.x; u < NT * PER; u += 256) {
-    const int t = u / PER, rr = (u % PER) >> 4, col = u & 15;
-    const int row = rbase + 16 * (EPI == EPI_SWIGLU ? t / (CT / 2) : t / CT) + rr;
-    if (row >= rend) continue;
-    const int e = (rr & 3) * 64 + (rr >> 2) * 16 + col;
-    auto sum = [&](int k) {
-      float y = (red[0][k][e] + red[1][k][e]) + (red[2][k][e] + red[3][k][e]);
-      if (PACK) y += (red[0][k][e + 32] + red[1][k][e + 32]) + (red[2][k][e + 32] + red[3][k][e + 32]);   // row + 8
-      return y;
-    };
-    if (EPI == EPI_F32) {
-      a.out[(size_t)s * a.out_split + (size_t)row * a.N + (tile0 + t % CT) * 16 + col] = sum(t);
-    } else {
-      // tiles (2p, 2p+1) are (gate, up) of the same 16 hidden units
-      const int m = t / (CT / 2), p = t % (CT / 2);
-      const float g = sum(m * CT + 2 * p), up = sum(m * CT + 2 * p + 1);
-      store_split(a.hout, a.h_lo, (size_t)row * (a.N >> 1) + ((tile0 >> 1) + p) * 16 + col, g / (1.f + __expf(-g)) * up);
+    for (int i = 0; i < 4; ++i) {
+      const int row = rbase + 16 * m + rq + i;
+      if (row >= rend) continue;
+      if (EPI == EPI_F32) {
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+          a.out[(size_t)s * a.out_split + (size_t)row * a.N + (tile0 + j) * 16 + col] = acc[m][j][i];
+      } else {
+        // tiles (2p, 2p+1) are (gate, up) of the same 16 hidden units
+#pragma unroll
+        for (int p = 0; p < CT / 2; ++p)
+          store_split(a.hout, a.h_lo, (size_t)row * (a.N >> 1) + ((tile0 >> 1) + p) * 16 + col,
+                      silu_mul(acc[m][2 * p][i], acc[m][2 * p + 1][i]));
+      }
     }
-  }
 }
 
 // -------------------------------- row GEMMs of steps with very few rows
@@ -819,7 +843,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_mm(GemmArgs a, int nwg) {
           const int row = rbase + r * 16 + rq + i;
           if (row < rend) {
             const float g = acc[r][2 * q][i], u = acc[r][2 * q + 1][i];
-            store_split(a.hout, a.h_lo, (size_t)row * half + ((nt0 >> 1) + q) * 16 + col, g / (1.f + __expf(-g)) * u);
+            store_split(a.hout, a.h_lo, (size_t)row * half + ((nt0 >> 1) + q) * 16 + col, silu_mul(g, u));
           }
         }
   }
@@ -979,7 +1003,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_big(GemmArgs a, int nwg) {
           const int row = rbase + r * 16 + rq + i;
           if (row < rend) {
             const float g = acc[r][2 * q][i], u = acc[r][2 * q + 1][i];
-            store_split(a.hout, a.h_lo, (size_t)row * half + ((nt0 >> 1) + q) * 16 + col, g / (1.f + __expf(-g)) * u);
+            store_split(a.hout, a.h_lo, (size_t)row * half + ((nt0 >> 1) + q) * 16 + col, silu_mul(g, u));
           }
         }
   }
@@ -1942,30 +1966,41 @@ hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, in
     return hipErrorInvalidValue;
   }
   if (bf16 && mt >= kWgTile) {
-    const int m = mt - kWgTile;          // rows / 16
-    // every wave takes a quarter of a split, in whole k-steps
-    if (a.ksteps < 4 || a.ksteps % 4 != 0 || nt < 1 || a.N % (64 * nt) != 0) return hipErrorInvalidValue;
-    auto go = [&](auto kern, int cols) {
-      const int nblk = a.total_items * (64 * nt / cols);
-      klaunch(kern, dim3((nblk + 7) / 8 * 8), dim3(256), st, a, nblk, 64 * nt);
-    };
-    if (m == 1 && nt == 2) {
-      for (int g = 0; g < a.ngroups; ++g)
-        if (a.g[g].nrows > 8) return hipErrorInvalidValue;
-      if (epi == EPI_SWIGLU) go(k_gemm_sm<1, 2, 4, EPI_SWIGLU, true, 4>, 32);
-      else go(k_gemm_sm<1, 2, 4, EPI_F32, true, 4>, 32);
-    } else if (m == 1 && nt == 4) {
-      if (epi == EPI_SWIGLU) go(k_gemm_sm<1, 4, 2, EPI_SWIGLU, false, 4>, 64);
-      else go(k_gemm_sm<1, 4, 2, EPI_F32, false, 4>, 64);
-    } else if (m == 2 && nt == 2) {
-      if (epi == EPI_SWIGLU) go(k_gemm_sm<2, 4, 2, EPI_SWIGLU, false, 3>, 64);
-      else go(k_gemm_sm<2, 4, 2, EPI_F32, false, 3>, 64);
-    } else if (m == 4 && nt == 2) {
-      if (epi == EPI_SWIGLU) go(k_gemm_sm<4, 4, 2, EPI_SWIGLU, false, 2>, 64);
-      else go(k_gemm_sm<4, 4, 2, EPI_F32, false, 2>, 64);
-    } else {
+    const int m = mt - kWgTile;          // row tiles of a workgroup
+    if ((m != 1 && m != 2 && m != 4) || (nt != 8 && nt != 4 && (nt != 2 || epi != EPI_F32)) || a.N % (16 * nt) != 0)
       return hipErrorInvalidValue;
-    }
+    // whole stages of four k-steps, equal splits
+    if (a.ksteps < 4 || a.ksteps % 4 != 0 || a.ksteps * a.S * 32 != a.K) return hipErrorInvalidValue;
+    auto go = [&](auto kern, int nw) {
+      klaunch(kern, dim3((a.total_items + 7) / 8 * 8), dim3(64 * nw), st, a, a.total_items);
+    };
+    auto tile = [&](auto wr, auto ct, auto nw, auto e) {
+      constexpr int M = decltype(wr)::value, CT = decltype(ct)::value, NW = decltype(nw)::value, E = decltype(e)::value;
+      // two stages of weights ahead where there are few waves with long chains (one
+      // 1B model with ffn 6528, whose down has 128 waves of 204 k-steps: 299 us a step
+      // at 12 rows, 313 with one stage); more waves want the registers (1B, 16 rows:
+      // 254, 251 with one)
+      if (a.ksteps >= 12 && a.total_items * NW < 512) go(k_gemm_sm<M, CT, NW, 2, E>, NW);
+      else go(k_gemm_sm<M, CT, NW, 1, E>, NW);
+    };
+    auto rows = [&](auto wr) {
+      using One = std::integral_constant<int, 1>;
+      using Two = std::integral_constant<int, 2>;
+      using Four = std::integral_constant<int, 4>;
+      const std::integral_constant<int, EPI_SWIGLU> swiglu;
+      const std::integral_constant<int, EPI_F32> f32;
+      if (epi == EPI_SWIGLU) {
+        if (nt == 8) tile(wr, Two{}, Four{}, swiglu);
+        else tile(wr, Two{}, Two{}, swiglu);
+      } else {
+        if (nt == 8) tile(wr, Two{}, Four{}, f32);
+        else if (nt == 4) tile(wr, One{}, Four{}, f32);
+        else tile(wr, One{}, Two{}, f32);
+      }
+    };
+    if (m == 1) rows(std::integral_constant<int, 1>{});
+    else if (m == 2) rows(std::integral_constant<int, 2>{});
+    else rows(std::integral_constant<int, 4>{});
     return hipGetLastError();
   }
   if (!bf16) {

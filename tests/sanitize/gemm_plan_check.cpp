@@ -9,7 +9,7 @@
 //     then row chunk / column block / k-split) over every item of the grid
 //     covers every (row, column block, k-split) of every carried group exactly
 //     once, with no item resolving to an empty group or an empty row range;
-//   * the k-splits tile the reduction dimension (the workgroup-tile kernel's
+//   * the k-splits tile the reduction dimension (the small-M kernel's
 //     equal splits of whole 4-step stages, the medium-M kernel's rounded ones);
 //   * split-K partials stay inside the engine's partial buffer;
 //   * a share's launch picks the same tiling, split and partial stride as the
@@ -51,7 +51,7 @@ struct Proj { const char* name; int K, N, epi; bool split; bool lm; };
 struct Shape { const char* name; moa_model_cfg m; };
 
 // The tile geometry a (mt, nt) code stands for, as the launcher reads it.
-struct Tile { int kind; int rows; int cols; int S; };   // kind 0 f32, 1 workgroup-tile, 2 medium-M
+struct Tile { int kind; int rows; int cols; int S; };   // kind 0 f32, 1 small-M, 2 medium-M
 
 bool dispatchable(bool bf16, const GemmArgs& a, int epi, int mt, int nt, Tile& t, const char* what) {
   const int KS = a.K / 32;
@@ -78,12 +78,12 @@ bool dispatchable(bool bf16, const GemmArgs& a, int epi, int mt, int nt, Tile& t
   }
   CHECK(mt >= kWgTile, "%s: unknown tile code %d", what, mt);
   const int m = mt - kWgTile;
-  CHECK(m == 1 || m == 2 || m == 4, "%s: workgroup-tile rows %d", what, m);
-  CHECK(nt == 4 || nt == 2 || (nt == 1 && epi == EPI_F32), "%s: workgroup-tile nt %d", what, nt);
+  CHECK(m == 1 || m == 2 || m == 4, "%s: small-M rows %d", what, m);
+  CHECK(nt == 8 || nt == 4 || (nt == 2 && epi == EPI_F32), "%s: small-M nt %d", what, nt);
   CHECK(a.ksteps % 4 == 0 && a.ksteps > 0, "%s: ksteps %d", what, a.ksteps);
   CHECK(a.ksteps * a.S == KS, "%s: %d splits of %d != %d k-steps", what, a.S, a.ksteps, KS);
-  CHECK(a.N % (64 * nt) == 0, "%s: N %d nt %d", what, a.N, nt);
-  t = {1, 16 * m, 64 * nt, a.S};
+  CHECK(a.N % (16 * nt) == 0, "%s: N %d nt %d", what, a.N, nt);
+  t = {1, 16 * m, 16 * nt, a.S};
   return true;
 }
 

@@ -35,6 +35,11 @@ def _batch(lens, shape, G=3, of=None, budget=512, sharp=False):
     return dict(lens=list(lens), shape=shape, G=G, of=list(of or [0] * len(lens)), budget=budget, sharp=sharp)
 
 
+def _rows(shape, *rows, G=4):
+    """Every step has rows[m] rows of model m: one-token prompts, all of G tokens."""
+    return _batch([1] * sum(rows), shape, G=G, of=[m for m, n in enumerate(rows) for _ in range(n)])
+
+
 _ragged = [1, 31, 32, 33, 63, 64, 65, 97, 127, 128, 129, 161, 7, 12, 13, 45, 200, 300, 5, 82]
 BATCHES = {
     # prefill attention: one step of more than 256 rows and 20 prompts, every edge of its tiles of 32 keys and 128 rows
@@ -42,6 +47,16 @@ BATCHES = {
     "prompts hd128": _batch(_ragged, (2, 512, 4, 2, 128, 256, 512), G=1, budget=2048),
     "sharp prompts hd64": _batch(_ragged, (1, 512, 4, 2, 64, 256, 512), G=1, budget=2048, sharp=True),
     "sharp prompts hd128": _batch(_ragged, (1, 512, 8, 2, 128, 256, 512), G=1, budget=2048, sharp=True),
+    # small-M GEMM: 7 to 16 rows, one model and several; K/32 with few and many twos; prompts whose last rows alone
+    # reach the head; a qkv width of whole 128-column tiles only, at any number of rows
+    "rows 7": _rows((2, 512, 8, 2, 64, 1408, 1152), 7),
+    "rows 8": _rows((1, 2048, 32, 8, 64, 5632, 1152), 8),
+    "rows 9": _rows((1, 2048, 16, 2, 128, 8192, 1024), 9),
+    "rows 16": _rows((2, 256, 4, 1, 64, 1408, 512), 16),
+    "rows 12 5": _rows((1, 1536, 16, 2, 128, 1024, 1152), 12, 5),
+    "rows 8 8 8": _rows((1, 4096, 8, 2, 128, 896, 512), 8, 8, 8),
+    "chunked prompts hd128": _batch([700, 650, 600], (2, 512, 4, 2, 128, 256, 512), G=1, budget=333),
+    "qkv 384": _batch([300, 290], (1, 512, 4, 1, 64, 256, 512), G=1, of=[0, 1], budget=1024),
 }
 
 
