@@ -31,12 +31,14 @@ constexpr int kBigTargetWgs = 256;  // one workgroup per CU
 // sums costs kPartialUs to write and, in the consumer, to read back.
 constexpr double kRoundUs = 1.075, kGridUs = 0.442, kPartialUs = 0.37e-6;
 // Steps of up to this many rows run on the row GEMMs (at most kRowMax rows per
-// model). us per step of four layers, split-K GEMMs with norm and RoPE launches ->
-// row GEMMs: 8B 414 -> 383 at 1 row, 427 -> 403 at 4, 443 -> 425 at 6, 455 -> 466 at
-// 8; 1B 213 -> 185, 225 -> 205, 231 -> 221, 233 -> 237; three 8B models 910 -> 893 at 2
-// rows each, 930 -> 936 at 4; three 1B models 374 -> 338, 381 -> 354: every row is one
-// more read of the activations for each 16 or 32 columns.
-constexpr int kRowSteps = 6;
+// model). us per step of four layers, small-M GEMMs with norm and RoPE launches ->
+// row GEMMs (the same bits): 8B 433 -> 379 at 1 row, 442 -> 409 at 4, 451 -> 431 at
+// 6, 446 -> 458 at 8; 1B 229 -> 185, 238 -> 213, 241 -> 228, 235 -> 243; three 8B
+// models 979 -> 923 at 2 rows each; d 1,536 with ffn 8,960, two models of 4 rows 311
+// -> 247. O and down have d / 16 workgroups with a wave per k-split, so a long K on
+// a narrow d is left out: d 512, ffn 14,336 is 167 -> 158 at 1 row (rows * ffn / d =
+// 28), 175 -> 175 at 3 (84), 180 -> 197 at 6 (168); the widths above stay below 25.
+constexpr int kRowSteps = 6, kRowDepth = 64;
 static_assert(kRowSteps <= kRowMax, "row GEMM rows");
 // bf16 steps with several models run them on up to this many streams: the
 // step's models are dealt out in shares of about equal cost (rows laid out
@@ -124,7 +126,7 @@ struct Layout {
   size_t model_bytes, kv_bytes, block_bytes;
   size_t off_xpart[kMaxShares - 1];   // split-K partials of shares 1.. (0: none)
   size_t off_kv, off_tok, off_bt, off_rope, off_meta, off_x, off_xn, off_part, off_q, off_ao, off_h,
-      off_logits, off_xl, off_ss, off_pacc, off_pml, off_models, total;
+      off_logits, off_xl, off_pacc, off_pml, off_models, total;
   int64_t token_store, block_store, meta_ints;
 };
 
@@ -202,8 +204,6 @@ Layout make_layout(const moa_engine_cfg& c) {
   L.off_logits = take((size_t)L.Rmax * V * 4);
   // LM-head input (final-norm output in LM-row order; split pair in bf16)
   L.off_xl = take((size_t)2 * L.Rmax * d * L.esz);
-  // sums of squares of the row GEMMs' output rows
-  L.off_ss = take((size_t)kRowSteps * (d / 16) * 4);
   L.off_pacc = take((size_t)L.slots_cap * nh * hd * 4);
   L.off_pml = take((size_t)L.slots_cap * nh * 2 * 4);
   L.off_models = off;
@@ -255,7 +255,6 @@ struct moa_engine {
   void* h = nullptr;
   float* logits = nullptr;
   void* xl = nullptr;                 // LM-head input rows (final norm output)
-  float* ss = nullptr;                // sums of squares between row GEMMs
   float* pacc = nullptr;
   float* pml = nullptr;
   void* scratch = nullptr;            // this GPU's library scratch array (moa_step_noalloc)
@@ -728,7 +727,6 @@ moa_status moa_create(const moa_engine_cfg* cfg, void* dev_arena, size_t arena_b
     e->h = A + L.off_h;
     e->logits = (float*)(A + L.off_logits);
     e->xl = A + L.off_xl;
-    e->ss = (float*)(A + L.off_ss);
     e->pacc = (float*)(A + L.off_pacc);
     e->pml = (float*)(A + L.off_pml);
     hipError_t err = hipStreamCreateWithFlags(&e->copy_stream, hipStreamNonBlocking);
@@ -1260,9 +1258,8 @@ moa_status enqueue_step(moa_engine* e, const std::vector<int64_t>& admitted, int
     }
     // A step of very few rows (counted over all models, so that every share
     // decides alike): the row GEMMs take over the norms, residuals and RoPE between
-    // the layers' GEMMs. Layer 0 starts from a norm launch, and the final norm reads
-    // the finished residual.
-    const bool row_gemms = bf && T <= kRowSteps;
+    // the layers' GEMMs; the final norm reads the finished residual.
+    const bool row_gemms = bf && T <= kRowSteps && (int64_t)T * F <= (int64_t)kRowDepth * d;
     for (int l = 0; l < g.n_layers; ++l) {
       for (int u = 0; u < nshare; ++u) {
         Share& b = sh[u];
@@ -1273,9 +1270,12 @@ moa_status enqueue_step(moa_engine* e, const std::vector<int64_t>& admitted, int
         GemmArgs ga;
         int mt, nt;
         bool lg;
-        auto row_gemm = [&](auto get, const void* X, size_t x_lo, int K, int N) {
+        // a row GEMM of the share, on the k-split of the whole step
+        auto row_gemm = [&](auto get, const void* X, size_t x_lo, int K, int N, bool split) {
           GemmArgs r{};
           r.ngroups = b.ng;
+          int maxM = 0, totalM = 0;
+          for (int k = 0; k < gin.ngroups; ++k) { maxM = std::max(maxM, gin.nrows[k]); totalM += gin.nrows[k]; }
           for (int k = 0; k < b.ng; ++k) {
             r.g[k].W = get(e->models[gmodel[b.g0 + k]]);
             r.g[k].row0 = gin.row0[b.g0 + k];
@@ -1285,27 +1285,28 @@ moa_status enqueue_step(moa_engine* e, const std::vector<int64_t>& admitted, int
           r.x_lo = x_lo;
           r.K = K;
           r.N = N;
+          r.S = split ? small_split(e, gin, maxM, totalM, K, N) : 1;
+          r.ksteps = K / 32 / r.S;
           return r;
         };
         RowArgs ra{};
         if (row_gemms) {
           ra.x = e->x;
-          ra.xn = (uint16_t*)e->xn;
-          ra.xn_lo = xn_lo;
-          ra.ss = e->ss;
-          ra.ss_in = e->ss;
           ra.d = d;
           ra.eps = g.rms_eps;
         }
-        if (!row_gemms || l == 0)
+        auto row_norm = [&](auto get) {
+          for (int k = 0; k < b.ng; ++k) ra.gamma.p[k] = get(e->models[gmodel[b.g0 + k]]);
+        };
+        if (!row_gemms)
           LAUNCH(MOA_K_NORM, norm_bytes + b.prev_split * (double)b.nr * d * 4.0, 0,
                launch_add_rmsnorm(st, bf, e->x + ro * d, b.prev_split ? b.part + ro * d : nullptr, b.prev_split,
                                   b.prev_stride, nullptr, sd.row_model + ro, b.nr,
                                   fill([l](const ModelDev& x) { return x.attn_norm[l]; }), xn_b, xn_lo, d,
                                   g.rms_eps), "attn norm");
         if (row_gemms) {
+          row_norm([l](const ModelDev& x) { return x.attn_norm[l]; });
           RowArgs rq = ra;
-          rq.ss_in = l == 0 ? nullptr : e->ss;
           rq.row_pos = sd.row_pos;
           rq.row_bt = sd.row_bt;
           rq.bt_store = e->bt_store;
@@ -1317,7 +1318,7 @@ moa_status enqueue_step(moa_engine* e, const std::vector<int64_t>& admitted, int
           rq.n_h = nh;
           rq.n_kv = nkv;
           rq.hd = hd;
-          ga = row_gemm([l](const ModelDev& x) { return x.wqkv[l]; }, e->xn, xn_lo, d, qkv);
+          ga = row_gemm([l](const ModelDev& x) { return x.wqkv[l]; }, nullptr, 0, d, qkv, true);
           gemm_cost(ga, EPI_F32, gb, gf);
           LAUNCH_GEMM(MOA_K_GEMM_QKV, false, gb, gf, launch_gemm_row(st, ga, rq, ROW_ROPE), "qkv row gemm");
         } else {
@@ -1344,20 +1345,16 @@ moa_status enqueue_step(moa_engine* e, const std::vector<int64_t>& admitted, int
           LAUNCH(MOA_K_ATTN_REDUCE, b.red_bytes, 0,
                  launch_attn_reduce(st, bf, b.red, b.nred, pacc, pml, e->ao, ao_lo, nh, hd), "attn reduce");
         if (row_gemms) {
-          for (int k = 0; k < b.ng; ++k) ra.gamma.p[k] = e->models[gmodel[b.g0 + k]].mlp_norm[l];
-          ga = row_gemm([l](const ModelDev& x) { return x.wo[l]; }, e->ao, ao_lo, nh * hd, d);
+          ga = row_gemm([l](const ModelDev& x) { return x.wo[l]; }, e->ao, ao_lo, nh * hd, d, true);
           gemm_cost(ga, EPI_F32, gb, gf);
           LAUNCH_GEMM(MOA_K_GEMM_O, false, gb, gf, launch_gemm_row(st, ga, ra, ROW_RES), "o row gemm");
-          ga = row_gemm([l](const ModelDev& x) { return x.wgu[l]; }, e->xn, xn_lo, d, 2 * F);
+          row_norm([l](const ModelDev& x) { return x.mlp_norm[l]; });
+          ga = row_gemm([l](const ModelDev& x) { return x.wgu[l]; }, nullptr, 0, d, 2 * F, false);
           ga.hout = (uint16_t*)e->h;
           ga.h_lo = h_lo;
           gemm_cost(ga, EPI_SWIGLU, gb, gf);
           LAUNCH_GEMM(MOA_K_GEMM_GATEUP, false, gb, gf, launch_gemm_row(st, ga, ra, ROW_SWIGLU), "gate-up row gemm");
-          for (int k = 0; k < b.ng; ++k) {
-            const ModelDev& m = e->models[gmodel[b.g0 + k]];
-            ra.gamma.p[k] = l + 1 < g.n_layers ? m.attn_norm[l + 1] : m.final_norm;
-          }
-          ga = row_gemm([l](const ModelDev& x) { return x.wdown[l]; }, e->h, h_lo, F, d);
+          ga = row_gemm([l](const ModelDev& x) { return x.wdown[l]; }, e->h, h_lo, F, d, true);
           gemm_cost(ga, EPI_F32, gb, gf);
           LAUNCH_GEMM(MOA_K_GEMM_DOWN, false, gb, gf, launch_gemm_row(st, ga, ra, ROW_RES), "down row gemm");
           continue;

@@ -59,22 +59,17 @@ constexpr int kMmTile = 3000;
 
 // Steps of very few rows run their layers on row GEMMs (k_gemm_row; at most
 // kRowMax rows per group) that also do the work of the norm and RoPE kernels
-// between them; `a` needs only the groups (W, row0, nrows), X, x_lo, K, N and hout.
-//  ROW_RES: x += X.W^T; xn = split(x * gamma), not yet normalised;
-//           ss[row][N / 16] = sums of squares of x over 16 columns.
-//  ROW_SWIGLU, ROW_ROPE: X = such an xn, so each sum is scaled by
-//           rsqrt(mean square of the row + eps) from ss (ss_in; null: X is
-//           normalised already); then SwiGLU to hout, or RoPE, q and the KV append.
+// between them; `a` needs only the groups (W, row0, nrows), K, N, the k-split
+// (S * ksteps == K / 32, S <= 16) and what the epilogue names.
+//  ROW_RES: x += X.W^T (X: split pair, x_lo).
+//  ROW_SWIGLU, ROW_ROPE: the input is norm(x) * gamma (K == d); then SwiGLU to
+//           hout (S == 1), or RoPE, q and the KV append.
 constexpr int kRowMax = 8;
 enum RowEpilogue { ROW_RES = 0, ROW_SWIGLU = 1, ROW_ROPE = 2 };
 struct RowArgs {
-  ModelPtrs gamma;     // ROW_RES: per group, the gains of the next norm
-  float* x;
-  uint16_t* xn;
-  size_t xn_lo;
-  float* ss;
-  const float* ss_in;
-  int d;               // row length of x (ss and ss_in rows hold d / 16 values)
+  ModelPtrs gamma;     // per group, the norm's gains
+  float* x;            // residual rows
+  int d;               // their length (d % 256 == 0, d <= 4096)
   float eps;
   const int *row_pos, *row_bt, *bt_store;
   const float2* rope_tab;
@@ -82,7 +77,7 @@ struct RowArgs {
   void* kv;
   int layer, num_blocks, n_h, n_kv, hd;
 };
-hipError_t launch_gemm_row(hipStream_t st, GemmArgs a, const RowArgs& f, int epi);
+hipError_t launch_gemm_row(hipStream_t st, const GemmArgs& a, const RowArgs& f, int epi);
 
 // Attention work item: one query row against keys [k0, k1) of its request.
 // bt_off: index in the block store of the block holding key k0 (k0 is a

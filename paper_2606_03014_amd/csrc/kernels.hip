@@ -109,6 +109,25 @@ __device__ __forceinline__ float silu_mul(float g, float up) {
   return g / (1.f + __expf(-g)) * up;
 }
 
+// The norm's and RoPE's arithmetic, with every fused operation written out: the
+// kernels that share it give the same bits whatever the compiler would fuse.
+__device__ __forceinline__ float sumsq4(float4 v) {
+  return fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.x, v.x, v.y * v.y)));
+}
+// split pairs of (v * scale) * g for four elements: h01, h23 | l01, l23
+__device__ __forceinline__ u32x4 norm_split4(float4 v, float scale, const float g[4]) {
+#pragma clang fp contract(off)
+  const float t0 = v.x * scale, t1 = v.y * scale, t2 = v.z * scale, t3 = v.w * scale;
+  const unsigned h0 = pack_bf16(t0 * g[0], t1 * g[1]), h1 = pack_bf16(t2 * g[2], t3 * g[3]);
+  const unsigned l0 = pack_bf16(fmaf(t0, g[0], -__uint_as_float(h0 << 16)), fmaf(t1, g[1], -__uint_as_float(h0 & 0xffff0000u)));
+  const unsigned l1 = pack_bf16(fmaf(t2, g[2], -__uint_as_float(h1 << 16)), fmaf(t3, g[3], -__uint_as_float(h1 & 0xffff0000u)));
+  return u32x4{h0, h1, l0, l1};
+}
+__device__ __forceinline__ float2 rotate(float x1, float x2, float2 cs) {
+#pragma clang fp contract(off)
+  return make_float2(fmaf(x1, cs.x, -(x2 * cs.y)), fmaf(x2, cs.x, x1 * cs.y));
+}
+
 // Order this wavefront's LDS writes before its later LDS reads (no workgroup barrier).
 __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -254,7 +273,7 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(float* __restrict__ x, con
   }
   float ss = 0.f;
 #pragma unroll
-  for (int k = 0; k < V4; ++k) ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
+  for (int k = 0; k < V4; ++k) ss += sumsq4(v[k]);
   ss = wave_sum(ss);
   const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   if ((threadIdx.x & 63) == 0) red[w] = ss;
@@ -265,18 +284,15 @@ __global__ __launch_bounds__(1024) void k_add_rmsnorm(float* __restrict__ x, con
 #pragma unroll
   for (int k = 0; k < V4; ++k) {
     const int i = (threadIdx.x + k * blockDim.x) * 4;
-    const float y[4] = {v[k].x * scale * gv[k][0], v[k].y * scale * gv[k][1], v[k].z * scale * gv[k][2],
-                        v[k].w * scale * gv[k][3]};
     if (BF) {
       // split-bf16 pairs packed in hardware, one 8-byte store per plane
-      unsigned h01, l01, h23, l23;
-      split_pair(y[0], y[1], h01, l01);
-      split_pair(y[2], y[3], h23, l23);
+      const u32x4 y = norm_split4(v[k], scale, gv[k]);
       uint16_t* o = (uint16_t*)out + (size_t)j * d + i;
-      *(uint2*)o = make_uint2(h01, h23);
-      *(uint2*)(o + out_lo) = make_uint2(l01, l23);
+      *(uint2*)o = make_uint2(y.x, y.y);
+      *(uint2*)(o + out_lo) = make_uint2(y.z, y.w);
     } else {
-      *(float4*)((float*)out + (size_t)j * d + i) = make_float4(y[0], y[1], y[2], y[3]);
+      *(float4*)((float*)out + (size_t)j * d + i) = make_float4(v[k].x * scale * gv[k][0], v[k].y * scale * gv[k][1],
+                                                                v[k].z * scale * gv[k][2], v[k].w * scale * gv[k][3]);
     }
   }
 }
@@ -440,173 +456,6 @@ __global__ __launch_bounds__(64 * NW, 2) void k_gemm_sm(GemmArgs a, int nblk) {
     }
 }
 
-// -------------------------------- row GEMMs of steps with very few rows
-// Up to 8 rows per model, a layer of nine launches spends as long on launches
-// and the short kernels between the GEMMs (5 us each for a norm or RoPE) as on the
-// 1B weights. Here no k-split crosses a workgroup (NW waves split k, 16 * CT columns
-// each, as in the small-M kernel with both planes packed), so the epilogue
-// holds finished sums and does the next kernel's work on them:
-//  * O and down add the residual and write x, x * gamma of the next norm as a
-//    split pair, and each 16 columns' sum of squares;
-//  * the consumer multiplies that pair unnormalised and scales its sums by the
-//    row's rsqrt(mean square): the scale commutes with the product;
-//  * qkv owns both halves of its rotation pairs (tiles hd / 2 columns apart).
-// A layer is then qkv, attention (and its combine), O, gate-up, down. Without the
-// cross-workgroup split the GEMMs lose 0-1 us each at 1 row and up to 7 at 8
-// (8B down 20 -> 27 us), against ~15 us saved per layer.
-template <int CT, int NW, int D, int EPI>
-__global__ __launch_bounds__(64 * NW, 4) void k_gemm_row(GemmArgs a, RowArgs f, int ncb) {
-  __shared__ float red[NW][CT][256];
-  __shared__ float rs[kRowMax];
-  const int nblk = ncb * a.ngroups;
-  const int per = (nblk + 7) / 8;
-  const int blk = (blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (blk >= nblk) return;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int g = blk / ncb, cb = blk - g * ncb;
-  const void* Wg = a.g[0].W;
-  const void* gam = f.gamma.p[0];
-  int row0 = a.g[0].row0, nrows = a.g[0].nrows;
-#pragma unroll
-  for (int i = 1; i < kMaxGroups; ++i)
-    if (i == g) { Wg = a.g[i].W; row0 = a.g[i].row0; nrows = a.g[i].nrows; gam = f.gamma.p[i]; }
-  const int KS = a.K >> 5;
-  const int ks0 = (w * KS) / NW, nk = ((w + 1) * KS) / NW - ks0;
-  int tile[CT];
-  int head = 0, j0 = 0;
-  if constexpr (EPI == ROW_ROPE) {
-    const int per_head = f.hd / 32;
-    head = cb / per_head;
-    const int u = cb - head * per_head;
-    j0 = u * 16;
-    tile[0] = head * (f.hd / 16) + u;
-    tile[CT - 1] = tile[0] + per_head;
-  } else {
-#pragma unroll
-    for (int c = 0; c < CT; ++c) tile[c] = cb * CT + c;
-  }
-  // the rows' scales: a part of each wave's lanes sums a row's 16-column squares
-  if constexpr (EPI != ROW_RES) {
-    constexpr int LPR = 64 * NW / kRowMax;            // lanes per row (32 or 64)
-    const int r = threadIdx.x / LPR, l = threadIdx.x % LPR;
-    float t = 0.f;
-    const int n = f.d >> 4;
-    if (f.ss_in && r < nrows)
-      for (int i = l; i < n; i += LPR) t += f.ss_in[(size_t)(row0 + r) * n + i];
-    t = sum16(t);
-    t += swz_xor16(t);
-    if constexpr (LPR == 64) t += __shfl_xor(t, 32, 64);
-    if (l == 0) rs[r] = f.ss_in ? rsqrtf(t / (float)f.d + f.eps) : 1.f;
-  }
-  const u32x4* bp[CT];
-#pragma unroll
-  for (int c = 0; c < CT; ++c) bp[c] = (const u32x4*)Wg + ((size_t)tile[c] * KS + ks0) * 64 + lane;
-  const int r16 = lane & 15;
-  const uint16_t* ap = (const uint16_t*)a.X + (size_t)(r16 >> 3) * a.x_lo +
-                       (size_t)(row0 + min(r16 & 7, nrows - 1)) * a.K + (size_t)ks0 * 32 + 8 * (lane >> 4);
-  f32x4_t acc[CT];
-#pragma unroll
-  for (int c = 0; c < CT; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  if (nk > 0) {                                       // wave-uniform
-    u32x4 b[D][CT], av[D];
-    auto load = [&](int st, int d) {
-#pragma unroll
-      for (int c = 0; c < CT; ++c) b[d][c] = load_stream(bp[c] + (size_t)st * 64);
-      av[d] = *(const u32x4*)(ap + st * 32);
-    };
-    auto mul = [&](int d) {
-#pragma unroll
-      for (int c = 0; c < CT; ++c)
-        acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av[d]),
-                                                         __builtin_bit_cast(bf16x8_t, b[d][c]), acc[c], 0, 0, 0);
-    };
-#pragma unroll
-    for (int d = 0; d < D; ++d) load(min(d, nk - 1), d);
-    int st = 0;
-    for (; st + D < nk; st += D) {
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        mul(d);
-        load(min(st + D + d, nk - 1), d);
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-      if (st + d < nk) mul(d);
-  }
-#pragma unroll
-  for (int c = 0; c < CT; ++c)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) red[w][c][i * 64 + lane] = acc[c][i];
-  __syncthreads();
-  if (threadIdx.x >= 16 * kRowMax) return;            // whole waves
-  const int rr = threadIdx.x >> 4, col = threadIdx.x & 15;
-  const bool live = rr < nrows;
-  const int row = row0 + rr;
-  const int e = (rr & 3) * 64 + (rr >> 2) * 16 + col; // hi plane; the lo plane's row + 8 is 32 further
-  float y[CT];
-#pragma unroll
-  for (int c = 0; c < CT; ++c) {
-    float v[NW];
-#pragma unroll
-    for (int k = 0; k < NW; ++k) v[k] = red[k][c][e] + red[k][c][e + 32];
-#pragma unroll
-    for (int k = NW / 2; k > 0; k /= 2)
-#pragma unroll
-      for (int i = 0; i < k; ++i) v[i] += v[i + k];
-    y[c] = v[0];
-  }
-  if constexpr (EPI == ROW_RES) {
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-      const int n = tile[c] * 16 + col;
-      const size_t o = (size_t)row * f.d + n;
-      float v = 0.f;
-      if (live) {
-        v = f.x[o] + y[c];
-        f.x[o] = v;
-        store_split(f.xn, f.xn_lo, o, v * bf2f(((const uint16_t*)gam)[n]));
-      }
-      const float t = sum16(v * v);
-      if (live && col == 0) f.ss[(size_t)row * (f.d >> 4) + tile[c]] = t;
-    }
-  } else if constexpr (EPI == ROW_SWIGLU) {
-    if (live) {
-#pragma unroll
-      for (int p = 0; p < CT / 2; ++p) {
-        const float gt = y[2 * p] * rs[rr], up = y[2 * p + 1] * rs[rr];
-        store_split(a.hout, a.h_lo, (size_t)row * (a.N >> 1) + (tile[2 * p] >> 1) * 16 + col,
-                    gt / (1.f + __expf(-gt)) * up);
-      }
-    }
-  } else if (live) {
-    const int half = f.hd >> 1, jj = j0 + col;
-    const float x1 = y[0] * rs[rr], x2 = y[CT - 1] * rs[rr];
-    const int pos = f.row_pos[row];
-    const size_t hs = (size_t)2 * kBlock * f.hd;
-    if (head < f.n_h + f.n_kv) {
-      const float2 cs = f.rope_tab[(size_t)pos * half + jj];
-      const float y1 = x1 * cs.x - x2 * cs.y, y2 = x2 * cs.x + x1 * cs.y;
-      if (head < f.n_h) {
-        const size_t o = ((size_t)row * f.n_h + head) * f.hd + jj;
-        f.q[o] = y1;
-        f.q[o + half] = y2;
-      } else {
-        const int b = f.bt_store[f.row_bt[row] + (pos >> 4)];
-        const size_t o = (((size_t)f.layer * f.num_blocks + b) * f.n_kv + (head - f.n_h)) * hs + (pos & 15) * f.hd + jj;
-        ((uint16_t*)f.kv)[o] = f2bf(y1);
-        ((uint16_t*)f.kv)[o + half] = f2bf(y2);
-      }
-    } else {
-      const int b = f.bt_store[f.row_bt[row] + (pos >> 4)];
-      const size_t o = (((size_t)f.layer * f.num_blocks + b) * f.n_kv + (head - f.n_h - f.n_kv)) * hs +
-                       (size_t)kBlock * f.hd + (pos & 15) * f.hd + jj;
-      ((uint16_t*)f.kv)[o] = f2bf(x1);
-      ((uint16_t*)f.kv)[o + half] = f2bf(x2);
-    }
-  }
-}
-
 // ---------------------------------------- wait, LDS and direct-load helpers
 // Explicit waits, LDS addressing and untracked LDS reads shared by the GEMM
 // and attention kernels below. Direct global->LDS loads
@@ -644,6 +493,226 @@ __device__ __forceinline__ void ds_write_b32(unsigned addr, unsigned v) {
 }
 // Wait for every outstanding LDS access; tying v makes its later uses follow.
 __device__ __forceinline__ void lgkm_wait_for(u32x4& v) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v)); }
+
+// -------------------------------- row GEMMs of steps with very few rows
+// Up to 8 rows per model, a layer of nine launches spends as long on launches
+// and the short kernels between the GEMMs (5 us each for a norm or RoPE) as on the
+// 1B weights. Here a workgroup holds all S k-splits of its columns, a wave each
+// (wave w < S * CG: split w % S of column group w / S), so its epilogue has finished
+// sums:
+//  * O and down add them to the residual;
+//  * qkv owns both halves of its rotation pairs (tiles hd / 2 columns apart) and
+//    writes q and the KV cache;
+//  * qkv and gate-up normalise their model's rows themselves, every workgroup all
+//    of them, into LDS as split pairs (d * 4 bytes a row), with eight waves at
+//    least, while the weights' first loads are in flight.
+// A layer is then qkv, attention (and its combine), O, gate-up, down. All sums run
+// in the order of the kernels that this replaces (a split's k-steps in one chain,
+// splits added in order to the residual, the norm's lanes and waves as in its own
+// launch), so the step's bits are theirs.
+// O and down read their rows' fragments from L2. Rows 0-7 of an A operand are the
+// hi plane and rows 8-15 the lo plane, so one load brings both; the other operand is
+// the same with the halves of 16 lanes swapped. Output rows 8-15 are not used.
+// us per launch at 1 and 6 rows, 1B: qkv 7.4 and 9.6 (norm, GEMM and RoPE launches
+// 14.7 and 15.1 at 8), gate-up 13.7 and 17.1 (18.6), down 9.0 and 12.4 (7.6 and a
+// norm); 8B at 6 rows: qkv 15.0, O 8.4, gate-up 42.4, down 22.8.
+constexpr int kRowPad = 4;                           // words between rows in LDS: other banks for each row
+template <int CT, int D, int EPI>
+__global__ __launch_bounds__(EPI == ROW_RES && D > 8 ? 256 : 1024) void k_gemm_row(GemmArgs a, RowArgs f, int ncb, int CG) {
+  extern __shared__ __align__(16) unsigned char row_smem[];
+  const int nblk = ncb * a.ngroups;
+  const int per = (nblk + 7) / 8;
+  const int blk = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (blk >= nblk) return;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  const int g = blk / ncb, cb = blk - g * ncb;
+  const void* Wg = a.g[0].W;
+  const void* gam = f.gamma.p[0];
+  int row0 = a.g[0].row0, nrows = a.g[0].nrows;
+#pragma unroll
+  for (int i = 1; i < kMaxGroups; ++i)
+    if (i == g) { Wg = a.g[i].W; row0 = a.g[i].row0; nrows = a.g[i].nrows; gam = f.gamma.p[i]; }
+  const int S = a.S, s = w % S, cg = w / S;
+  const bool mine = cg < CG;                         // the other waves only help to normalise
+  const int KS = a.K >> 5, nk = a.ksteps, ks0 = s * nk;
+  const int c0 = cb * CG + (mine ? cg : 0);          // this wave's columns
+  auto tile_of = [&](int c, int j) {                 // their j-th 16-column tile
+    if constexpr (EPI == ROW_ROPE) {
+      const int ph = f.hd / 32, head = c / ph;
+      return head * (f.hd / 16) + (c - head * ph) + j * ph;
+    } else {
+      return c * CT + j;
+    }
+  };
+  float* red = (float*)row_smem;                     // [wave][tile][256], where the rows were
+  const int d = f.d, stride = d + kRowPad;
+  float* xr = (float*)row_smem;                      // [row][stride]: x, then per 4 columns h01, h23, l01, l23
+  float* sums = xr + (size_t)nrows * stride;         // [row][norm wave]
+  // the norm launch's shape: waves of 64 lanes, V4 float4s per lane
+  const int v4 = (d % 2048 == 0) ? 2 : 1, nt = d / (4 * v4), nvw = nt >> 6;
+  uint2 gb[2];                                       // gains of columns 4 * (thread, thread + blockDim)
+  if constexpr (EPI != ROW_RES) {
+    for (int u = w; u < nrows * (d >> 8); u += nw) {
+      const int r = u / (d >> 8), c = (u - r * (d >> 8)) * 256;
+      __builtin_amdgcn_global_load_lds((const void*)(f.x + (size_t)(row0 + r) * d + c + 4 * lane),
+                                       MOA_LDS(xr + r * stride + c), 16, 0, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int i = (threadIdx.x + k * blockDim.x) * 4;
+      gb[k] = i < d ? *(const uint2*)((const uint16_t*)gam + i) : make_uint2(0, 0);
+    }
+  }
+  const u32x4* bp[CT];
+#pragma unroll
+  for (int j = 0; j < CT; ++j) bp[j] = (const u32x4*)Wg + ((size_t)tile_of(c0, j) * KS + ks0) * 64 + lane;
+  u32x4 b[D][CT], av[D];
+  const uint16_t* ap = (const uint16_t*)a.X + (size_t)((lane >> 3) & 1) * a.x_lo +
+                       (size_t)(row0 + min(lane & 7, nrows - 1)) * a.K + (size_t)ks0 * 32 + 8 * (lane >> 4);
+  auto load = [&](int st, int q) {
+#pragma unroll
+    for (int j = 0; j < CT; ++j) b[q][j] = load_stream(bp[j] + (size_t)st * 64);
+    if constexpr (EPI == ROW_RES) av[q] = *(const u32x4*)(ap + st * 32);
+  };
+  // LDS only: the loads in flight stay in flight
+  auto barrier = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  if constexpr (EPI != ROW_RES) wait_vmcnt<0>();     // this wave's part of the rows is in LDS
+  if (mine) {
+#pragma unroll
+    for (int q = 0; q < D; ++q) load(min(q, nk - 1), q);
+  }
+  if constexpr (EPI != ROW_RES) {
+    barrier();
+    for (int u = w; u < nrows * nvw; u += nw) {
+      const int r = u / nvw, t = (u - r * nvw) * 64 + lane;
+      const float* x = xr + r * stride + t * 4;
+      float ss = sumsq4(*(const float4*)x);
+      if (v4 == 2) ss += sumsq4(*(const float4*)(x + nt * 4));
+      ss = wave_sum(ss);
+      if (lane == 0) sums[r * 16 + (u - r * nvw)] = ss;
+    }
+    barrier();
+    float scale = 0.f;                               // of row `lane`
+    if (lane < nrows) {
+      float tot = 0.f;
+      for (int k = 0; k < nvw; ++k) tot += sums[lane * 16 + k];
+      scale = rsqrtf(tot / (float)d + f.eps);
+    }
+    for (int r = 0; r < nrows; ++r) {
+      const float sr = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, scale), r));
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int i = (threadIdx.x + k * blockDim.x) * 4;
+        if (i < d) {
+          const float gv[4] = {__uint_as_float(gb[k].x << 16), __uint_as_float(gb[k].x & 0xffff0000u),
+                               __uint_as_float(gb[k].y << 16), __uint_as_float(gb[k].y & 0xffff0000u)};
+          float* e = xr + r * stride + i;
+          *(u32x4*)e = norm_split4(*(const float4*)e, sr, gv);
+        }
+      }
+    }
+    barrier();
+  }
+  const uint2* ax = (const uint2*)(xr + min(lane & 15, nrows - 1) * stride + ks0 * 32 + 8 * (lane >> 4));
+  f32x4_t acc[CT];
+#pragma unroll
+  for (int j = 0; j < CT; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto mul = [&](int st, int q) {
+    u32x4 x[2];
+    if constexpr (EPI == ROW_RES) {
+      x[0] = av[q];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[1][k] = __builtin_amdgcn_mov_dpp(av[q][k], 0x128, 0xF, 0xF, true);   // lane ^ 8 of 16
+    } else {
+      const uint2 h0 = ax[st * 16], l0 = ax[st * 16 + 1], h1 = ax[st * 16 + 2], l1 = ax[st * 16 + 3];
+      x[0] = u32x4{h0.x, h0.y, h1.x, h1.y};
+      x[1] = u32x4{l0.x, l0.y, l1.x, l1.y};
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int j = 0; j < CT; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x[p]),
+                                                         __builtin_bit_cast(bf16x8_t, b[q][j]), acc[j], 0, 0, 0);
+  };
+  if (mine) {
+    int st = 0;
+    for (; st + D < nk; st += D) {
+#pragma unroll
+      for (int q = 0; q < D; ++q) {
+        mul(st + q, q);
+        load(min(st + D + q, nk - 1), q);
+        __builtin_amdgcn_sched_barrier(0);           // a fragment's registers are free before they are loaded again
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < D; ++q)
+      if (st + q < nk) mul(st + q, q);
+  }
+  if constexpr (EPI == ROW_SWIGLU) {
+    // S = 1: the wave's own sums; register i of lane l is row 4 (l / 16) + i, column l % 16
+    const int col = lane & 15, rq = (lane >> 4) * 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (mine && rq + i < nrows)
+#pragma unroll
+        for (int p = 0; p < CT / 2; ++p)
+          store_split(a.hout, a.h_lo, (size_t)(row0 + rq + i) * (a.N >> 1) + (c0 * (CT / 2) + p) * 16 + col,
+                      silu_mul(acc[2 * p][i], acc[2 * p + 1][i]));
+    return;
+  }
+  if constexpr (EPI != ROW_RES) barrier();           // every wave has read its rows
+  if (mine)
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) red[(w * CT + j) * 256 + i * 64 + lane] = acc[j][i];
+  barrier();
+  // output t of the workgroup: column group t / 128, row t / 16 % 8, column t % 16
+  for (int t = threadIdx.x; t < 128 * CG; t += blockDim.x) {
+    const int oc = t >> 7, rr = (t >> 4) & 7, col = t & 15;
+    if (rr >= nrows) continue;
+    const int row = row0 + rr;
+    const float* rp = red + (size_t)oc * S * CT * 256 + (rr & 3) * 64 + (rr >> 2) * 16 + col;
+    if constexpr (EPI == ROW_RES) {
+#pragma unroll
+      for (int j = 0; j < CT; ++j) {
+        float* o = f.x + (size_t)row * d + tile_of(cb * CG + oc, j) * 16 + col;
+        float v = *o;
+        for (int k = 0; k < S; ++k) v += rp[(k * CT + j) * 256];
+        *o = v;
+      }
+    } else {
+      const int c = cb * CG + oc, ph = f.hd / 32, head = c / ph;
+      const int half = f.hd >> 1, jj = (c - head * ph) * 16 + col;
+      float x1 = 0.f, x2 = 0.f;
+      for (int k = 0; k < S; ++k) {
+        x1 += rp[k * CT * 256];
+        x2 += rp[(k * CT + CT - 1) * 256];
+      }
+      const int pos = f.row_pos[row];
+      const size_t hs = (size_t)2 * kBlock * f.hd;
+      float2 y = make_float2(x1, x2);
+      if (head < f.n_h + f.n_kv) y = rotate(x1, x2, f.rope_tab[(size_t)pos * half + jj]);
+      if (head < f.n_h) {
+        const size_t o = ((size_t)row * f.n_h + head) * f.hd + jj;
+        f.q[o] = y.x;
+        f.q[o + half] = y.y;
+      } else {
+        const int kh = (head - f.n_h) % f.n_kv, kv_sel = (head - f.n_h) / f.n_kv;
+        const int bk = f.bt_store[f.row_bt[row] + (pos >> 4)];
+        const size_t o = (((size_t)f.layer * f.num_blocks + bk) * f.n_kv + kh) * hs + (size_t)kv_sel * kBlock * f.hd +
+                         (pos & 15) * f.hd + jj;
+        ((uint16_t*)f.kv)[o] = f2bf(y.x);
+        ((uint16_t*)f.kv)[o + half] = f2bf(y.y);
+      }
+    }
+  }
+}
 
 // -------------------------------------- medium-M GEMM (16x16x32 MFMA)
 // A few dozen to a few hundred rows per model. Every weight byte feeds only that
@@ -1120,8 +1189,8 @@ __global__ __launch_bounds__(256) void k_rope_kv(const float* __restrict__ part,
       x1 += pr[(size_t)s * split_stride + c];
       x2 += pr[(size_t)s * split_stride + c + half];
     }
-    const float y1 = x1 * cs.x - x2 * cs.y;
-    const float y2 = x2 * cs.x + x1 * cs.y;
+    const float2 y = rotate(x1, x2, cs);
+    const float y1 = y.x, y2 = y.y;
     if (head < n_h) {
       const size_t o = ((size_t)t * n_h + head) * hd + jj;
       qv[o] = y1;
@@ -2021,22 +2090,57 @@ hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, in
   return hipErrorInvalidValue;                        // no bf16 kernel for this tile code
 }
 
-hipError_t launch_gemm_row(hipStream_t st, GemmArgs a, const RowArgs& f, int epi) {
+hipError_t launch_gemm_row(hipStream_t st, const GemmArgs& a, const RowArgs& f, int epi) {
   if (a.ngroups < 1) return hipSuccess;
-  if (a.K % 32 != 0 || a.N % 32 != 0) return hipErrorInvalidValue;
-  for (int g = 0; g < a.ngroups; ++g)
+  if (a.S < 1 || a.S > 16 || a.ksteps < 1 || a.S * a.ksteps * 32 != a.K || a.N % 128 != 0) return hipErrorInvalidValue;
+  if (f.d % 256 != 0 || f.d > 4096) return hipErrorInvalidValue;
+  int rows = 0;
+  for (int g = 0; g < a.ngroups; ++g) {
     if (a.g[g].nrows < 1 || a.g[g].nrows > kRowMax) return hipErrorInvalidValue;
-  auto go = [&](auto kern, int cols, int threads) {
+    rows = std::max(rows, a.g[g].nrows);
+  }
+  static bool attr = false;                // one attribute call per process for the kernels that hold rows in LDS
+  if (!attr) {
+    for (const void* k : {(const void*)k_gemm_row<2, 8, ROW_SWIGLU>, (const void*)k_gemm_row<2, 4, ROW_SWIGLU>,
+                          (const void*)k_gemm_row<2, 8, ROW_ROPE>, (const void*)k_gemm_row<2, 4, ROW_ROPE>}) {
+      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 144 * 1024);
+      if (e != hipSuccess) return e;
+    }
+    attr = true;
+  }
+  // the rows and their sums (at most 129 KB), or after them the waves' partial sums
+  const unsigned norm = (unsigned)(rows * (f.d + kRowPad) + kRowMax * 16) * 4;
+  auto go = [&](auto kern, int ct, int cg, int waves, unsigned shm) {
+    const int cols = 16 * ct * cg;
+    if (a.N % cols != 0) return hipErrorInvalidValue;
     const int ncb = a.N / cols, nblk = ncb * a.ngroups;
-    klaunch(kern, dim3((nblk + 7) / 8 * 8), dim3(threads), st, a, f, ncb);
+    klaunch_shm(kern, dim3((nblk + 7) / 8 * 8), dim3(64 * waves), shm, st, a, f, ncb, cg);
+    return hipGetLastError();
   };
-  // O and down own 16 columns (at d 4096 one workgroup per CU), qkv and gate-up
-  // 32; gate-up has workgroups enough without an eight-way k-split
-  if (epi == ROW_RES && a.N == f.d) go(k_gemm_row<1, 8, 4, ROW_RES>, 16, 512);
-  else if (epi == ROW_SWIGLU) go(k_gemm_row<2, 4, 4, ROW_SWIGLU>, 32, 256);
-  else if (epi == ROW_ROPE && a.N == (f.n_h + 2 * f.n_kv) * f.hd && f.hd % 32 == 0) go(k_gemm_row<2, 8, 4, ROW_ROPE>, 32, 512);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  const bool deep = a.ksteps >= 8;                   // k-steps in flight: 8 or 4
+  if (epi == ROW_RES && a.N == f.d) {
+    // a column tile per workgroup; few splits are long chains in few waves, which
+    // keep 16 k-steps in flight
+    const unsigned sums = (unsigned)a.S * 1024;
+    if (a.S <= 4 && a.ksteps >= 16) return go(k_gemm_row<1, 16, ROW_RES>, 1, 1, a.S, sums);
+    if (deep) return go(k_gemm_row<1, 8, ROW_RES>, 1, 1, a.S, sums);
+    return go(k_gemm_row<1, 4, ROW_RES>, 1, 1, a.S, sums);
+  }
+  if (a.K != f.d) return hipErrorInvalidValue;
+  if (epi == ROW_SWIGLU && a.S == 1) {
+    // 128 columns per workgroup, 64 where that leaves CUs idle
+    const int cg = a.ngroups * (a.N / 128) >= 224 ? 4 : 2;
+    if (deep) return go(k_gemm_row<2, 8, ROW_SWIGLU>, 2, cg, 8, norm);
+    return go(k_gemm_row<2, 4, ROW_SWIGLU>, 2, cg, 8, norm);
+  }
+  if (epi == ROW_ROPE && a.N == (f.n_h + 2 * f.n_kv) * f.hd && f.hd % 64 == 0) {
+    const int cg = a.S >= 4 ? 1 : 4 / a.S;
+    const int waves = std::max(8, a.S * cg);
+    const unsigned shm = std::max(norm, (unsigned)(2 * a.S * cg) * 1024);
+    if (deep) return go(k_gemm_row<2, 8, ROW_ROPE>, 2, cg, waves, shm);
+    return go(k_gemm_row<2, 4, ROW_ROPE>, 2, cg, waves, shm);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_rope_kv(hipStream_t st, bool bf16, const float* part, int nsplit, size_t split_stride,

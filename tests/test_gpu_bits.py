@@ -57,6 +57,16 @@ BATCHES = {
     "rows 8 8 8": _rows((1, 4096, 8, 2, 128, 896, 512), 8, 8, 8),
     "chunked prompts hd128": _batch([700, 650, 600], (2, 512, 4, 2, 128, 256, 512), G=1, budget=333),
     "qkv 384": _batch([300, 290], (1, 512, 4, 1, 64, 256, 512), G=1, of=[0, 1], budget=1024),
+    # row GEMMs: steps of up to six rows; K of 8 to 448 k-steps, both head widths, one to eight query heads per KV
+    # head, prompts of a few tokens prefilled in such steps, several models on two streams, a deep ffn on a narrow d
+    # on either side of the rule
+    "row 1": _rows((3, 2048, 32, 8, 64, 8192, 1152), 1, G=6),
+    "row 6": _rows((2, 512, 2, 2, 128, 1408, 512), 6, G=6),
+    "rows 2 3 1": _rows((2, 256, 8, 1, 64, 128, 512), 2, 3, 1, G=6),
+    "rows 2 deep": _rows((1, 512, 8, 2, 64, 14336, 512), 2),
+    "rows 3 deep": _rows((1, 512, 8, 2, 64, 14336, 512), 3),
+    "row 4096": _rows((1, 4096, 32, 8, 128, 14336, 512), 2),
+    "short prompts": _batch([3, 1, 2, 5, 1], (2, 1536, 12, 12, 64, 1024, 1152), G=5, of=[0, 1, 0, 1, 1], budget=4),
 }
 
 
