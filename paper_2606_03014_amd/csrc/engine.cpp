@@ -535,12 +535,15 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
   // the medium-M kernel.
   //  * Whole 16-row tiles of a group per workgroup: RT tiles per row chunk,
   //    2 up to 32 rows, 4 up to 64, else 8.
-  //  * 8 waves over 512 columns, or over 256 at RT = 8, 4 waves over 256 below (a
-  //    vocabulary of 128,256 is 501 x 256, and two 64-row chunks per model would
-  //    stream its LM head twice); F32 projections choose between them below.
-  //  * About one workgroup per CU. Gate-up (no k-split: its SwiGLU epilogue needs
-  //    the whole sum) takes the first tile shape whose grid has 150..256
-  //    workgroups, else the small-M kernel.
+  //  * 8 waves over 512 columns where N allows; otherwise 8 waves over 256
+  //    at RT = 8 and 4 waves over 256 below (a vocabulary of 128,256 is
+  //    501 x 256, and two 64-row chunks per model would stream its LM head
+  //    twice).
+  //  * About one workgroup per CU. F32 projections take the k-split that
+  //    brings this grid nearest ~224 workgroups; gate-up (no k-split: its
+  //    SwiGLU epilogue needs the whole sum) takes the first tile shape whose
+  //    grid has 150..256 workgroups, else the small-M kernel.
+  int sm_split = 0;                        // k-split of an F32 projection handed to the small-M kernel
   if (maxM > 16 && N % 256 == 0) {
     struct Shape { int rt, nw, ct; };
     auto chunks_of = [&](int rt) {
@@ -560,39 +563,24 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
         if (items >= 150 && items <= 256) { sh = c; break; }
       }
     } else {
-      // F32 projections: columns per workgroup and k-split together, on the sum
-      // of the GEMM and its consumer's read of the partials (cold weights; swept
-      // over 256 and 512 columns and S = 2..16 at 24 to 260 rows in one to four
-      // groups of both widths; us of plan "512 columns at ~224 workgroups" -> this):
-      //  * 512 columns (fewest activation reads) while a split keeps 20 k-steps (12
-      //    up to 64 rows, where 256 columns mean four waves, too few beside another
-      //    stream: a four-layer step of four 8B models at 60 rows 1,896 us, 2,024 with
-      //    20 there): 8B down, three models at 90/70/50 rows 93 (108 on 256 columns).
-      //  * else 256 columns and half the splits, at ~224 workgroups, or as many as
-      //    fit one per CU for a long K (past 32 rows): 8B o at 88 rows 25.1 -> 23.0, down 48.0 ->
-      //    39.9; 1B qkv of three models at 90/70/50 26.8 -> 22.6, o 23.6 -> 19.9.
-      //  * where even 16 splits of 256 columns leave CUs idle, the small-M kernel,
-      //    which splits k inside its workgroups: 1B o at 60 rows 17.9 -> 12.6, qkv
-      //    20.1 -> 14.5, down 25.9 -> 20.6; 8B o at 24 rows 17.2 -> 14.5. Not past 64
-      //    rows for a long K (1B down at 88 rows: 29.3, 24.6 here).
-      const Shape wide = (rt0 >= 4 && N % 512 == 0) ? Shape{rt0, 8, 4} : Shape{0, 0, 0};
-      const Shape narrow = rt0 == 8 ? Shape{8, 8, 2} : Shape{rt0, 4, 4};
-      const int nb_rows = chunks_of(rt0), base256 = nb_rows * (N / 256);
-      sh = wide.rt ? wide : narrow;
+      sh = (rt0 >= 4 && N % 512 == 0) ? Shape{rt0, 8, 4} : (rt0 == 8 ? Shape{8, 8, 2} : Shape{rt0, 4, 4});
       if (allow_split) {
-        auto bounded = [&](int s) {
-          s = std::max(1, std::min(16, s));
-          while (s > 1 && ((int64_t)s * totalM * N > e->lay.part_cap || s > KS)) --s;
-          return s;
-        };
-        const int base = std::max(1, nb_rows * (N / (16 * sh.nw * sh.ct)));
-        S = bounded((224 + base / 2) / base);
-        const bool idle = base256 * 16 <= (maxM <= 32 ? 256 : 192);
-        if (idle && maxM <= 128 && (K <= 4096 || maxM <= 64)) {
+        const int base = chunks_of(sh.rt) * (N / (16 * sh.nw * sh.ct));
+        S = std::max(1, std::min(16, (224 + base / 2) / std::max(base, 1)));
+        while (S > 1 && ((int64_t)S * totalM * N > e->lay.part_cap || S > KS)) --S;
+        // S stands, whatever runs it: it fixes the order of the sums. Where 16 splits
+        // still leave half the CUs idle, the same splits go to the small-M kernel's
+        // narrower workgroups if they are whole stages (us per step of four 1B layers:
+        // 24 rows 299 -> 285, 60 rows 464 -> 408), else to 256 columns (8B, two to four
+        // layers: 96 rows 975 -> 926, 128 rows 1,142 -> 1,044; 1B at 96 rows 561 -> 521;
+        // ffn 6528, 48 rows 434 -> 404). Past these grids the wide tiles read the
+        // activations less often (three 1B models at 90 rows: 817, 833 on 256 columns).
+        const int items = base * S;
+        if (items <= (maxM <= 32 ? 128 : 64) && maxM <= 64 && KS % (4 * S) == 0) {
           sh = Shape{0, 0, 0};
-        } else if (!wide.rt || KS < (rt0 == 8 ? 20 : 12) * S || base * 16 < 192) {
-          sh = narrow;
-          S = bounded(KS >= 256 && rt0 > 2 ? 256 / base256 : (224 + base256 / 2) / base256);
+          sm_split = S;
+        } else if (sh.nw == 8 && sh.ct == 4 && items <= 128) {
+          sh = rt0 == 8 ? Shape{8, 8, 2} : Shape{rt0, 4, 4};
         }
       }
     }
@@ -643,7 +631,7 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
   // twice them 272
   const int wmt = maxM <= 16 ? 1 : (maxM <= 32 ? 2 : 4);
   const int rows_per = 16 * wmt;
-  const int S = allow_split ? small_split(e, in, maxM, totalM, K, N) : 1;
+  const int S = sm_split ? sm_split : allow_split ? small_split(e, in, maxM, totalM, K, N) : 1;
   int chunks = 0;
   for (int g = 0; g < in.ngroups; ++g) chunks += (in.nrows[g] + rows_per - 1) / rows_per;
   mt = kWgTile + wmt;

@@ -67,6 +67,15 @@ BATCHES = {
     "rows 3 deep": _rows((1, 512, 8, 2, 64, 14336, 512), 3),
     "row 4096": _rows((1, 4096, 32, 8, 128, 14336, 512), 2),
     "short prompts": _batch([3, 1, 2, 5, 1], (2, 1536, 12, 12, 64, 1024, 1152), G=5, of=[0, 1, 0, 1, 1], budget=4),
+    # medium rows: k-splits of every projection between 17 rows and the large-row plan, ffn / 128 odd and even
+    "rows 17": _rows((1, 2048, 32, 8, 64, 5504, 1024), 17),
+    "rows 24": _rows((2, 1536, 8, 2, 128, 8960, 1024), 24),
+    "rows 48": _rows((1, 2048, 32, 8, 64, 6528, 1152), 48, G=3),
+    "rows 60": _rows((1, 2048, 32, 8, 64, 8192, 1024), 60, G=3),
+    "rows 96": _rows((1, 2048, 32, 8, 64, 8192, 512), 96, G=3),
+    "rows 90 70 50": _rows((1, 1024, 8, 4, 64, 1792, 512), 90, 70, 50, G=3),
+    "rows 130 20": _rows((1, 4096, 8, 2, 64, 1792, 512), 130, 20, G=2),
+    "rows 200": _rows((1, 512, 8, 2, 64, 896, 512), 200, G=2),
 }
 
 
