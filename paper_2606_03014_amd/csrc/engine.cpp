@@ -485,16 +485,12 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
   for (int g = 0; g < in.ngroups; ++g)
     if (in.nrows[g] > 0) minM = std::min(minM, in.nrows[g]);
   if ((maxM >= kBigMinRows || minM >= big_min) && N % 256 == 0) {
-    // matrix-core bound: the medium-M kernel on whole 128-row chunks, 8
-    // waves over 512 columns (256 where N is not a multiple of 512) with a
-    // three-stage weight ring.
-    // Measured against a 32x32-MFMA kernel that staged both operands in LDS
-    // (128 x 512 tiles): 3-29% faster from 512 to 16k rows on 8B shapes, and
-    // more where small groups share the launch (no padded rows multiplied).
+    // matrix-core bound: the large-M kernel on whole 128-row chunks, 8 waves
+    // over 512 columns (256 where N is not a multiple of 512).
     large = true;
     const int ct = N % 512 == 0 ? 4 : 2;
     mt = kMmTile + 8;
-    nt = 16 + ct;
+    nt = 24 + ct;
     const int ncol = N / (128 * ct);
     int base = 0;
     for (int g = 0; g < in.ngroups; ++g) base += ((in.nrows[g] + 127) / 128) * ncol;
@@ -603,9 +599,20 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
           T = t;
         }
       mt = kMmTile + sh.rt;
-      // 8 waves: gate-up at RT = 8 with the three-stage weight ring (1-2%
-      // faster there; the F32 projections' shorter k-splits prefer two)
-      nt = sh.nw == 8 ? (epi == EPI_SWIGLU && sh.rt == 8 ? 16 : 8) + sh.ct : sh.ct;
+      // Chunks: a group's balanced share of at most T tiles
+      auto chunk = [&](int g) {
+        const int tg = std::max(1, tiles(g)), nch = (tg + T - 1) / T;
+        return 16 * ((tg + nch - 1) / nch);
+      };
+      // Gate-up at RT = 8: the large-M kernel where every chunk of the step is
+      // whole; shorter ones keep this kernel, which skips padding tiles without
+      // losing its schedule (8B gate-up at 110/90/60 rows: 177 us, 190 on the
+      // other), with the three-stage weight ring (1-2% faster there; the F32
+      // projections' shorter k-splits prefer two). All give the same bits.
+      const bool deep = epi == EPI_SWIGLU && sh.rt == 8 && sh.nw == 8;
+      large = deep;
+      for (int g = 0; g < in.ngroups; ++g) large = large && (in.nrows[g] == 0 || chunk(g) == 128);
+      nt = sh.nw == 8 ? (large ? 24 : (deep ? 16 : 8)) + sh.ct : sh.ct;
       a.S = S;
       a.ksteps = KS / S;                   // informational: split s takes k-steps [s*KS/S, (s+1)*KS/S)
       a.out_split = (size_t)totalM * N;
@@ -613,9 +620,7 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
       for (int k = 0; k < ng; ++k) {
         const int g = g0 + k;
         a.g[k].W = in.W[g]; a.g[k].row0 = in.row0[g]; a.g[k].nrows = in.nrows[g];
-        const int tg = std::max(1, tiles(g));
-        const int nch = (tg + T - 1) / T;
-        a.g[k].mrows = 16 * ((tg + nch - 1) / nch);          // balanced chunks of at most T tiles
+        a.g[k].mrows = chunk(g);
         a.g[k].n_mc = (in.nrows[g] + a.g[k].mrows - 1) / a.g[k].mrows;   // 0 for an empty group
         a.g[k].item0 = item;
         item += a.g[k].n_mc * S * ncol;

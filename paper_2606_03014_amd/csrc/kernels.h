@@ -51,9 +51,9 @@ constexpr int kWgTile = 1000;
 // rows (RT = 2, 4 or 8) x NW*CT*16 columns x one of S k-splits of K/32/S
 // k-steps (rounded; 1 <= S <= K/32), with nt = CT (NW = 4 waves, RT <= 4;
 // CT = 2 or 4), nt = 8 + CT (NW = 8 waves; CT = 4 with RT >= 4, CT = 2
-// with RT = 8) or nt = 16 + CT (NW = 8 waves, RT = 8, CT = 2 or 4: the large-M
-// kernel where every group's mrows is 128, else, SwiGLU only, a three-stage weight
-// register ring);
+// with RT = 8), nt = 16 + CT (NW = 8 waves, RT = 8, CT = 2 or 4, SwiGLU only: a
+// three-stage weight register ring) or nt = 24 + CT (NW = 8 waves, RT = 8, CT = 2
+// or 4, every mrows 128 or 0 rows: the large-M kernel);
 // N must be a multiple of the columns.
 constexpr int kMmTile = 3000;
 

@@ -1989,8 +1989,8 @@ static hipError_t gemm_big(hipStream_t st, const GemmArgs& a) {
   return hipGetLastError();
 }
 
-// nt: CT (4 waves), 8 + CT (8 waves) or 16 + CT (8 waves, large-M kernel or a
-// three-stage weight ring); see kMmTile
+// nt: CT (4 waves), 8 + CT (8 waves), 16 + CT (8 waves, three-stage weight ring)
+// or 24 + CT (8 waves, the large-M kernel); see kMmTile
 template <int RT, int EPI>
 static hipError_t gemm_mm_nt(hipStream_t st, const GemmArgs& a, int nt) {
   if constexpr (RT <= 4)                          // 4 waves x RT = 8 x CT = 4: one wave per SIMD
@@ -2000,15 +2000,14 @@ static hipError_t gemm_mm_nt(hipStream_t st, const GemmArgs& a, int nt) {
     if (nt == 12) return gemm_mm<RT, 4, 8, (RT >= 8 ? 2 : 3), EPI>(st, a);
     if constexpr (RT >= 8) {
       if (nt == 10) return gemm_mm<RT, 2, 8, 3, EPI>(st, a);
-      if (nt == 18 || nt == 20) {
-        // whole 128-row chunks: the large-M kernel. Shorter ones (medium-row
-        // gate-up) keep the medium-M kernel, which skips padding tiles without
-        // losing its schedule (8B gate-up at 110/90/60 rows: 177 us, 190 on the
-        // other). Both give the same bits.
-        bool whole = true;
-        for (int g = 0; g < a.ngroups; ++g) whole = whole && a.g[g].mrows == 128;
-        if (whole) return nt == 18 ? gemm_big<2, EPI>(st, a) : gemm_big<4, EPI>(st, a);
-        if constexpr (EPI == EPI_SWIGLU) return nt == 18 ? gemm_mm<RT, 2, 8, 3, EPI>(st, a) : gemm_mm<RT, 4, 8, 3, EPI>(st, a);
+      if constexpr (EPI == EPI_SWIGLU) {
+        if (nt == 18) return gemm_mm<RT, 2, 8, 3, EPI>(st, a);
+        if (nt == 20) return gemm_mm<RT, 4, 8, 3, EPI>(st, a);
+      }
+      if (nt == 26 || nt == 28) {
+        for (int g = 0; g < a.ngroups; ++g)
+          if (a.g[g].nrows > 0 && a.g[g].mrows != 128) return hipErrorInvalidValue;
+        return nt == 26 ? gemm_big<2, EPI>(st, a) : gemm_big<4, EPI>(st, a);
       }
     }
   }

@@ -64,10 +64,14 @@ bool dispatchable(bool bf16, const GemmArgs& a, int epi, int mt, int nt, Tile& t
   if (mt > kMmTile && mt <= kMmTile + 8) {
     const int rt = mt - kMmTile;
     CHECK(rt == 2 || rt == 4 || rt == 8, "%s: RT %d", what, rt);
-    const bool ok = (rt <= 4 && nt == 4) || nt == 2 || (rt >= 4 && nt == 12) ||
-                    (rt >= 8 && (nt == 10 || nt == 18 || nt == 20));
-    CHECK(ok, "%s: no medium-M instantiation for RT %d nt %d", what, rt, nt);
-    const int cols = nt > 16 ? 8 * 16 * (nt - 16) : (nt > 8 ? 8 * 16 * (nt - 8) : 4 * 16 * nt);
+    const bool big = rt == 8 && (nt == 26 || nt == 28);
+    const bool ok = (rt <= 4 && nt == 4) || nt == 2 || (rt >= 4 && nt == 12) || (rt >= 8 && nt == 10) ||
+                    (rt >= 8 && epi == EPI_SWIGLU && (nt == 18 || nt == 20)) || big;
+    CHECK(ok, "%s: no medium- or large-M instantiation for RT %d nt %d epilogue %d", what, rt, nt, epi);
+    for (int g = 0; g < a.ngroups; ++g)
+      CHECK(!big || a.g[g].nrows == 0 || a.g[g].mrows == 128, "%s: large-M chunk of %d rows", what, a.g[g].mrows);
+    const int ct = nt > 24 ? nt - 24 : (nt > 16 ? nt - 16 : (nt > 8 ? nt - 8 : nt));
+    const int cols = (nt > 8 ? 8 : 4) * 16 * ct;
     CHECK(a.S >= 1 && a.S <= KS, "%s: S %d of %d k-steps", what, a.S, KS);
     CHECK(a.N % cols == 0, "%s: N %d not a multiple of %d", what, a.N, cols);
     for (int g = 0; g < a.ngroups; ++g)
@@ -159,12 +163,8 @@ bool check_case(const moa_engine& e, const Proj& p, const GemmPlanIn& in, const 
   Tile t;
   if (!dispatchable(e.bf16, whole, p.epi, mt, nt, t, what)) return false;
   if (!covers(whole, t, what)) return false;
-  // the large-M plan: whole 128-row chunks on the three-stage 8-wave code
-  // (medium gate-up at RT = 8 uses that code too, on smaller chunks)
-  if (large) {
-    CHECK(e.bf16 && mt == kMmTile + 8 && nt > 16, "%s: large plan on mt %d nt %d", what, mt, nt);
-    for (int g = 0; g < whole.ngroups; ++g) CHECK(whole.g[g].mrows == 128, "%s: large chunk %d", what, whole.g[g].mrows);
-  }
+  // launches are counted as large by the kernel that runs them
+  CHECK(large == (e.bf16 && mt == kMmTile + 8 && nt > 24), "%s: large %d on mt %d nt %d", what, large, mt, nt);
   if (!p.split) CHECK(whole.S == 1, "%s: unsplit projection split %d ways", what, whole.S);
   if (p.epi == EPI_SWIGLU && t.kind == 2 && !large)
     CHECK(whole.total_items <= 256, "%s: gate-up medium grid %d", what, whole.total_items);
