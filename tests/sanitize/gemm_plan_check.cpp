@@ -1,12 +1,14 @@
 // Host-side check of the grouped-GEMM planner against the launch contract of
 // the GEMM kernels. It includes the engine's source (the planner is internal
 // to it) and, for random ragged row mixes on the 8B, 1B and a small model's
-// projection shapes in both engine dtypes, plans every projection of a step,
+// projection shapes and on ffn widths with K / 32 poor in twos, in both engine
+// dtypes, plans every projection of a step,
 // whole and split into contiguous model-stream shares, then checks:
 //   * the tile code is one the GEMM launcher dispatches, with the divisibility
 //     and k-split bounds it enforces;
 //   * replaying each kernel's own item decode (group lookup by first item,
-//     then row chunk / column block / k-split) over every item of the grid
+//     then row chunk / column block / k-split, with the fp32 kernel's column
+//     sub-blocks and SwiGLU tile pairs) over every item of the grid
 //     covers every (row, column block, k-split) of every carried group exactly
 //     once, with no item resolving to an empty group or an empty row range;
 //   * the k-splits tile the reduction dimension (the small-M kernel's
@@ -16,7 +18,11 @@
 //     whole step, so its partials land where the step's consumer reads them;
 //   * gate-up (SwiGLU epilogue) is never split and, on the medium-M kernel,
 //     fits one workgroup per CU;
-//   * the large-M k-split still picks the splits measured best on the GPU.
+//   * the large-M k-split still picks the splits measured best on the GPU;
+//   * a split projection whose k can be split has waves enough in flight;
+//   * the row GEMMs' column groups, tiles and splits cover every column of a
+//     projection (for RoPE, both halves of every rotation pair in one wave) once,
+//     within the workgroup and the LDS that their launcher gives them.
 // The decode below restates the kernels' index arithmetic: a change to either
 // side that breaks the contract fails here, on the CPU. No HIP call is made.
 #include "../../paper_2606_03014_amd/csrc/engine.cpp"
@@ -56,7 +62,7 @@ struct Tile { int kind; int rows; int cols; int S; };   // kind 0 f32, 1 small-M
 bool dispatchable(bool bf16, const GemmArgs& a, int epi, int mt, int nt, Tile& t, const char* what) {
   const int KS = a.K / 32;
   if (!bf16) {
-    CHECK(a.N % 64 == 0, "%s: f32 N %d", what, a.N);
+    CHECK(a.N % 64 == 0 && a.K % 64 == 0, "%s: f32 N %d K %d", what, a.N, a.K);
     CHECK(a.S == 1, "%s: f32 split %d", what, a.S);
     t = {0, 16, 64, 1};
     return true;
@@ -88,6 +94,62 @@ bool dispatchable(bool bf16, const GemmArgs& a, int epi, int mt, int nt, Tile& t
   CHECK(a.ksteps * a.S == KS, "%s: %d splits of %d != %d k-steps", what, a.S, a.ksteps, KS);
   CHECK(a.N % (16 * nt) == 0, "%s: N %d nt %d", what, a.N, nt);
   t = {1, 16 * m, 16 * nt, a.S};
+  return true;
+}
+
+// The fp32 kernel's columns: SUB workgroups per 64-column item with CT 16-column
+// tiles each (CT = 4 from 1,024 items on, else 1, 2 for SwiGLU, whose tiles 2p and
+// 2p + 1 are the gate and up columns of one 16 of the N / 2 hidden units).
+bool f32_columns(const GemmArgs& a, int epi, const char* what) {
+  const int CT = a.total_items >= 1024 ? 4 : (epi == EPI_SWIGLU ? 2 : 1), SUB = 4 / CT;
+  std::vector<uint8_t> hit(a.N, 0);
+  for (int nb = 0; nb < a.N / 64; ++nb)
+    for (int sub = 0; sub < SUB; ++sub) {
+      const int tile0 = nb * 4 + sub * CT;
+      for (int c = 0; c < CT; ++c) {
+        const int col0 = epi == EPI_SWIGLU ? (tile0 / 2 + c / 2) * 16 + (c & 1) * (a.N / 2) : (tile0 + c) * 16;
+        for (int k = 0; k < 16; ++k) {
+          CHECK(col0 + k < a.N && !hit[col0 + k], "%s: f32 column %d of %d", what, col0 + k, a.N);
+          hit[col0 + k] = 1;
+        }
+      }
+    }
+  for (int c = 0; c < a.N; ++c) CHECK(hit[c], "%s: f32 column %d not covered", what, c);
+  return true;
+}
+
+// Row GEMMs: launch_gemm_row's choice for a projection of a step with at most
+// kRowSteps rows, and k_gemm_row's tile map.
+bool row_gemm(const moa_engine& e, const GemmPlanIn& in, int K, int N, int kind, const char* what) {
+  const moa_model_cfg& m = e.cfg.model;
+  int maxM = 0, totalM = 0, groups = 0;
+  for (int g = 0; g < in.ngroups; ++g) {
+    maxM = std::max(maxM, in.nrows[g]);
+    totalM += in.nrows[g];
+    groups += in.nrows[g] > 0;
+  }
+  const int S = kind == ROW_SWIGLU ? 1 : small_split(&e, in, maxM, totalM, K, N), KS = K / 32;
+  CHECK(S >= 1 && S <= 16 && KS % S == 0, "%s: row split %d of %d k-steps", what, S, KS);
+  CHECK(kind == ROW_RES ? N == m.d_model : K == m.d_model, "%s: row K %d N %d", what, K, N);
+  const int ct = kind == ROW_RES ? 1 : 2;
+  const int cg = kind == ROW_RES ? 1 : (kind == ROW_SWIGLU ? (groups * (N / 128) >= 224 ? 4 : 2) : (S >= 4 ? 1 : 4 / S));
+  const int waves = kind == ROW_RES ? S : (kind == ROW_SWIGLU ? 8 : std::max(8, S * cg));
+  CHECK(waves <= 16 && S * cg <= waves, "%s: %d waves for %d splits of %d column groups", what, waves, S, cg);
+  CHECK(kind == ROW_RES || m.d_model <= waves * 64 * 4 * 2, "%s: d %d on %d waves", what, m.d_model, waves);
+  CHECK(kRowMax * (m.d_model + 4) * 4 + kRowMax * 64 <= 144 * 1024, "%s: LDS rows", what);
+  CHECK(N % (16 * ct * cg) == 0, "%s: row N %d in blocks of %d", what, N, 16 * ct * cg);
+  std::vector<uint8_t> hit(N / 16, 0);
+  for (int c = 0; c < N / (16 * ct); ++c)            // c = column block * cg + column group
+    for (int j = 0; j < ct; ++j) {
+      int tile = c * ct + j;
+      if (kind == ROW_ROPE) {
+        const int ph = m.head_dim / 32, head = c / ph;
+        tile = head * (m.head_dim / 16) + (c - head * ph) + j * ph;
+        CHECK(tile / (m.head_dim / 16) == head, "%s: rotation pair leaves head %d", what, head);
+      }
+      CHECK(tile < N / 16 && !hit[tile], "%s: row tile %d", what, tile);
+      hit[tile] = 1;
+    }
   return true;
 }
 
@@ -163,11 +225,27 @@ bool check_case(const moa_engine& e, const Proj& p, const GemmPlanIn& in, const 
   Tile t;
   if (!dispatchable(e.bf16, whole, p.epi, mt, nt, t, what)) return false;
   if (!covers(whole, t, what)) return false;
+  if (!e.bf16 && !f32_columns(whole, p.epi, what)) return false;
+  if (e.bf16 && !p.lm && totalM <= kRowSteps &&
+      !row_gemm(e, in, p.K, p.N, p.epi == EPI_SWIGLU ? ROW_SWIGLU : (p.name[0] == 'q' ? ROW_ROPE : ROW_RES), what))
+    return false;
   // launches are counted as large by the kernel that runs them
   CHECK(large == (e.bf16 && mt == kMmTile + 8 && nt > 24), "%s: large %d on mt %d nt %d", what, large, mt, nt);
   if (!p.split) CHECK(whole.S == 1, "%s: unsplit projection split %d ways", what, whole.S);
   if (p.epi == EPI_SWIGLU && t.kind == 2 && !large)
     CHECK(whole.total_items <= 256, "%s: gate-up medium grid %d", what, whole.total_items);
+  // up to 64 rows a split projection is a stream of weights: 256 waves or more,
+  // 32 columns each at most, unless k cannot be split so far (16 splits, 4 k-steps
+  // each; the small-M kernel splits by twos in stages of 8 k-steps)
+  if (e.bf16 && p.split && totalM <= 64) {
+    int maxM = 0, twos = 1;
+    for (int g = 0; g < in.ngroups; ++g) maxM = std::max(maxM, in.nrows[g]);
+    while (twos < 16 && (p.K / 32) % (twos * 16) == 0) twos *= 2;
+    const int can = maxM <= 16 ? twos : std::min(16, p.K / 128);
+    const int per = t.kind == 1 ? (nt >= 4 ? 4 : 2) : (nt > 8 ? 8 : 4);   // waves of a workgroup
+    CHECK(whole.total_items * per >= std::min(256, can * p.N / 64), "%s: %d items of %d waves, split %d", what,
+          whole.total_items, per, whole.S);
+  }
   if (whole.S > 1) {
     CHECK(whole.out_split == (size_t)totalM * p.N, "%s: partial stride %zu", what, whole.out_split);
     CHECK((int64_t)whole.S * totalM * p.N <= e.lay.part_cap, "%s: %d partials of %d x %d exceed %lld floats", what,
@@ -234,8 +312,9 @@ bool measured_splits() {
 }
 
 int rows_draw(int cap) {
-  switch (rnd(6)) {
+  switch (rnd(7)) {
     case 0: return 0;
+    case 6: return 1 + (int)rnd(3);
     case 1: return 1 + (int)rnd(16);
     case 2: return 17 + (int)rnd(48);
     case 3: return 65 + (int)rnd(191);
@@ -249,10 +328,13 @@ int rows_draw(int cap) {
 int main(int argc, char** argv) {
   const int cases = argc > 1 ? std::atoi(argv[1]) : 400;
   if (argc > 2) g_rng ^= std::strtoull(argv[2], nullptr, 10) * 0x9e3779b97f4a7c15ull;   // another seed
-  const Shape shapes[3] = {
+  const Shape shapes[6] = {
       {"8B", {32, 4096, 32, 8, 128, 14336, 128256, 500000.f, 1e-5f}},
       {"1B", {16, 2048, 32, 8, 64, 8192, 128256, 500000.f, 1e-5f}},
       {"small", {2, 256, 8, 2, 64, 512, 1024, 10000.f, 1e-5f}},
+      {"ffn 13952", {2, 4096, 32, 8, 128, 13952, 4096, 10000.f, 1e-5f}},
+      {"ffn 5504", {2, 2048, 32, 8, 64, 5504, 1152, 10000.f, 1e-5f}},
+      {"ffn 1408", {2, 512, 4, 1, 64, 1408, 1152, 10000.f, 1e-5f}},
   };
   const int prefill_caps[4] = {512, 2048, 8192, 16384};
   const int seq_caps[3] = {64, 256, 512};
@@ -280,7 +362,7 @@ int main(int argc, char** argv) {
         const Proj projs[5] = {
             {"qkv", m.d_model, qkv, EPI_F32, true, false},
             {"o", qd, m.d_model, EPI_F32, true, false},
-            {"gate-up", m.d_model, 2 * m.ffn_dim, e.bf16 ? EPI_SWIGLU : EPI_F32, false, false},
+            {"gate-up", m.d_model, 2 * m.ffn_dim, EPI_SWIGLU, false, false},
             {"down", m.ffn_dim, m.d_model, EPI_F32, true, false},
             {"lm head", m.d_model, m.vocab, EPI_F32, false, true},
         };

@@ -8,8 +8,8 @@ that drives MOA_FLAG_PLAN_ONLY engines through the C ABI
 (tests/sanitize/plan_driver.c). A plan-only engine makes no HIP call, so this
 runs without a GPU. The grouped-GEMM planner, which only runs when a step is
 enqueued on a GPU, is checked on its own by tests/sanitize/gemm_plan_check.cpp
-(it includes engine.cpp): random ragged row mixes on the 8B, 1B and a small
-model's projections, every plan replayed through the kernels' item decode for
+(it includes engine.cpp): random ragged row mixes on the 8B, 1B, a small and three odd-ffn
+models' projections, every plan replayed through the kernels' item decode for
 exact coverage, launchability and partial-buffer bounds, under the same two
 sanitizers. tests/sanitize/step_plan_check.cpp checks every step's attention,
 combine, prefill-block and LM-row lists of plan-only engines against the
@@ -124,7 +124,7 @@ def step_check(tmp_path_factory):
 
 
 def test_gemm_plans_cover_every_output_once_and_launch(plan_check):
-    # 120 random steps per (dtype, model shape): about 3,500 plans, every
+    # 120 random steps per (dtype, model shape): about 7,000 plans, every
     # share launch replayed item by item
     _run_check(plan_check, "120", "gemm_plan_check")
 
