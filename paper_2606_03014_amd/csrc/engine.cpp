@@ -169,11 +169,7 @@ Layout make_layout(const moa_engine_cfg& c) {
   L.red_cap = c.max_num_seqs;
   // split-K partials: a prefill-sized step unsplit, or a full decode batch
   // split up to 8 ways (a few hundred rows need the split to fill the CUs)
-  int64_t pc = std::max(L.Tmax, (int64_t)8 * c.max_num_seqs) * std::max(qkv, d);
-  // fp32 gate-up once wrote its sums here; an engine's allocation-free steps
-  // are still refused at the same sizes
-  if (c.dtype == MOA_F32) pc = std::max(pc, L.Tmax * 2 * F);
-  L.part_cap = pc;
+  L.part_cap = std::max(L.Tmax, (int64_t)8 * c.max_num_seqs) * std::max(qkv, d);
   L.token_store = c.token_store ? c.token_store : (int64_t)64 << 20;
   L.block_store = c.block_store ? c.block_store : (int64_t)16 << 20;
   L.meta_ints = 4 * L.Tmax + 2 * L.Rmax + 8 * L.items_cap + 4 * L.red_cap + 4 * L.Tmax + 4 * L.Rmax;

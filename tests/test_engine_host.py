@@ -179,6 +179,23 @@ def test_second_model_stream_reserves_one_partial_buffer():
             == M.moa_arena_bytes(engine_cfg(f.model, "f32", f.engine, 3, one_stream=True)))
 
 
+def test_fp32_engines_reserve_no_gate_up_partials():
+    """Gate-up writes its SwiGLU output itself in both dtypes: the partial sums an engine plans for do not grow with
+    ffn, so a wide ffn costs its weights and two planes of hidden units, and alone makes no step_noalloc refuse."""
+    from paper_2606_03014_amd.engine import engine_cfg
+    shapes = [ModelShape(n_layers=1, d_model=256, n_heads=4, n_kv_heads=4, head_dim=64, ffn_dim=f, vocab=512)
+              for f in (1024, 8192)]
+    consts = EngineConsts(num_kv_blocks=64, max_num_seqs=8, max_prefill_tokens=2048, max_model_len=512)
+    narrow, wide = (M.moa_arena_bytes(engine_cfg(s, "f32", consts, 1)) for s in shapes)
+    df = 8192 - 1024
+    grown = 3 * df * 256 * 4 + 2 * (2048 + 8) * df * 4
+    assert grown <= wide - narrow <= grown + 4096                 # regions start on 256-byte boundaries
+    eng = _dry(shapes[1], consts, 1, dtype="f32")                 # 2 * 8,192 columns of 2,056 rows would be 135 MB
+    eng.submit(np.arange(5, dtype=np.int32), 0, 2)
+    assert eng.step_noalloc().step == 0
+    eng.close()
+
+
 def test_model_stream_shares_are_greedy_cost_balanced():
     """A plan-only bf16 engine plans the model-stream split of a two-stream
     GPU engine. On every step of a skewed four-expert batch: the shares
