@@ -78,6 +78,10 @@ struct RowArgs {
   int layer, num_blocks, n_h, n_kv, hd;
 };
 hipError_t launch_gemm_row(hipStream_t st, const GemmArgs& a, const RowArgs& f, int epi);
+// What it launches: column tiles per wave, column groups and waves per workgroup,
+// bytes of LDS, k-steps in flight; false for arguments that it refuses.
+struct RowShape { int ct, cg, waves; unsigned lds; int depth; };
+bool row_gemm_shape(const GemmArgs& a, const RowArgs& f, int epi, RowShape& s);
 
 // Attention work item: one query row against keys [k0, k1) of its request.
 // bt_off: index in the block store of the block holding key k0 (k0 is a
@@ -115,6 +119,8 @@ hipError_t launch_add_rmsnorm(hipStream_t st, bool bf16, float* x, const float* 
                               ModelPtrs gamma, void* out, size_t out_lo, int d, float eps);
 
 hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, int mt, int nt);
+// The arguments that launch_gemm takes; it refuses all others.
+bool gemm_accepts(bool bf16, const GemmArgs& a, int epi, int mt, int nt);
 
 hipError_t launch_rope_kv(hipStream_t st, bool bf16, const float* part, int nsplit, size_t split_stride,
                           const int* row_pos, const int* row_bt, const int* bt_store,

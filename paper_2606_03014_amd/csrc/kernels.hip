@@ -2004,24 +2004,41 @@ static hipError_t gemm_mm_nt(hipStream_t st, const GemmArgs& a, int nt) {
         if (nt == 18) return gemm_mm<RT, 2, 8, 3, EPI>(st, a);
         if (nt == 20) return gemm_mm<RT, 4, 8, 3, EPI>(st, a);
       }
-      if (nt == 26 || nt == 28) {
-        for (int g = 0; g < a.ngroups; ++g)
-          if (a.g[g].nrows > 0 && a.g[g].mrows != 128) return hipErrorInvalidValue;
-        return nt == 26 ? gemm_big<2, EPI>(st, a) : gemm_big<4, EPI>(st, a);
-      }
+      if (nt == 26) return gemm_big<2, EPI>(st, a);
+      if (nt == 28) return gemm_big<4, EPI>(st, a);
     }
   }
   return hipErrorInvalidValue;
 }
 
+bool gemm_accepts(bool bf16, const GemmArgs& a, int epi, int mt, int nt) {
+  if (!bf16) return a.K % 64 == 0 && a.N % 64 == 0;
+  if (mt > kMmTile && mt <= kMmTile + 8) {           // 16*RT rows x (16 * NW * CT) columns
+    const int rt = mt - kMmTile;
+    const bool big = nt == 26 || nt == 28;
+    const int ct = nt < 8 ? nt : nt % 8;
+    if (rt != 2 && rt != 4 && rt != 8) return false;
+    if (nt != 2 && !(nt == 4 && rt <= 4) && !(nt == 12 && rt >= 4) && !(nt == 10 && rt == 8) &&
+        !((nt == 18 || nt == 20) && rt == 8 && epi == EPI_SWIGLU) && !(big && rt == 8))
+      return false;
+    if (a.S < 1 || a.S > (a.K >> 5) || a.N % ((nt < 8 ? 4 : 8) * 16 * ct) != 0) return false;
+    for (int g = 0; g < a.ngroups; ++g) {
+      if (a.g[g].mrows < 0 || a.g[g].mrows % 16 != 0 || a.g[g].mrows > 16 * rt) return false;
+      if (big && a.g[g].nrows > 0 && a.g[g].mrows != 128) return false;
+    }
+    return true;
+  }
+  const int m = mt - kWgTile;                        // row tiles of a workgroup
+  if ((m != 1 && m != 2 && m != 4) || (nt != 8 && nt != 4 && (nt != 2 || epi != EPI_F32))) return false;
+  // whole stages of four k-steps, equal splits
+  return a.N % (16 * nt) == 0 && a.S >= 1 && a.ksteps >= 4 && a.ksteps % 4 == 0 && a.ksteps * a.S * 32 == a.K;
+}
+
 hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, int mt, int nt) {
   if (a.total_items <= 0) return hipSuccess;
-  if (bf16 && mt > kMmTile && mt <= kMmTile + 8) {   // medium-M: 16*RT rows x (16 * NW * CT) columns
+  if (!gemm_accepts(bf16, a, epi, mt, nt)) return hipErrorInvalidValue;
+  if (bf16 && mt > kMmTile && mt <= kMmTile + 8) {
     const int rt = mt - kMmTile;
-    const int cols = nt > 16 ? 8 * 16 * (nt - 16) : (nt > 8 ? 8 * 16 * (nt - 8) : 4 * 16 * nt);
-    if (a.S < 1 || a.S > (a.K >> 5) || a.N % cols != 0) return hipErrorInvalidValue;
-    for (int g = 0; g < a.ngroups; ++g)
-      if (a.g[g].mrows < 0 || a.g[g].mrows % 16 != 0 || a.g[g].mrows > 16 * rt) return hipErrorInvalidValue;
     if (epi == EPI_SWIGLU) {
       if (rt == 2) return gemm_mm_nt<2, EPI_SWIGLU>(st, a, nt);
       if (rt == 4) return gemm_mm_nt<4, EPI_SWIGLU>(st, a, nt);
@@ -2034,11 +2051,7 @@ hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, in
     return hipErrorInvalidValue;
   }
   if (bf16 && mt >= kWgTile) {
-    const int m = mt - kWgTile;          // row tiles of a workgroup
-    if ((m != 1 && m != 2 && m != 4) || (nt != 8 && nt != 4 && (nt != 2 || epi != EPI_F32)) || a.N % (16 * nt) != 0)
-      return hipErrorInvalidValue;
-    // whole stages of four k-steps, equal splits
-    if (a.ksteps < 4 || a.ksteps % 4 != 0 || a.ksteps * a.S * 32 != a.K) return hipErrorInvalidValue;
+    const int m = mt - kWgTile;
     auto go = [&](auto kern, int nw) {
       klaunch(kern, dim3((a.total_items + 7) / 8 * 8), dim3(64 * nw), st, a, a.total_items);
     };
@@ -2072,7 +2085,6 @@ hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, in
     return hipGetLastError();
   }
   if (!bf16) {
-    if (a.K % 64 != 0 || a.N % 64 != 0) return hipErrorInvalidValue;
     // four column tiles per workgroup once that fills the chip four times over
     // (it reads each activation row a quarter as often), else one (SwiGLU: two)
     const bool wide = a.total_items >= 1024;
@@ -2089,15 +2101,36 @@ hipError_t launch_gemm(hipStream_t st, bool bf16, const GemmArgs& a, int epi, in
   return hipErrorInvalidValue;                        // no bf16 kernel for this tile code
 }
 
-hipError_t launch_gemm_row(hipStream_t st, const GemmArgs& a, const RowArgs& f, int epi) {
-  if (a.ngroups < 1) return hipSuccess;
-  if (a.S < 1 || a.S > 16 || a.ksteps < 1 || a.S * a.ksteps * 32 != a.K || a.N % 128 != 0) return hipErrorInvalidValue;
-  if (f.d % 256 != 0 || f.d > 4096) return hipErrorInvalidValue;
+bool row_gemm_shape(const GemmArgs& a, const RowArgs& f, int epi, RowShape& s) {
+  if (a.ngroups < 1 || a.S < 1 || a.S > 16 || a.ksteps < 1 || a.S * a.ksteps * 32 != a.K || a.N % 128 != 0) return false;
+  if (f.d % 256 != 0 || f.d > 4096) return false;
   int rows = 0;
   for (int g = 0; g < a.ngroups; ++g) {
-    if (a.g[g].nrows < 1 || a.g[g].nrows > kRowMax) return hipErrorInvalidValue;
+    if (a.g[g].nrows < 1 || a.g[g].nrows > kRowMax) return false;
     rows = std::max(rows, a.g[g].nrows);
   }
+  // the rows and their sums (at most 129 KB), or after them the waves' partial sums
+  const unsigned norm = (unsigned)(rows * (f.d + kRowPad) + kRowMax * 16) * 4;
+  if (epi == ROW_RES && a.N == f.d) {
+    // a column tile per workgroup; few splits are long chains in few waves, which
+    // keep 16 k-steps in flight
+    s = {1, 1, a.S, (unsigned)a.S * 1024, a.S <= 4 && a.ksteps >= 16 ? 16 : (a.ksteps >= 8 ? 8 : 4)};
+  } else if (epi == ROW_SWIGLU && a.K == f.d && a.S == 1) {
+    // 128 columns per workgroup, 64 where that leaves CUs idle
+    s = {2, a.ngroups * (a.N / 128) >= 224 ? 4 : 2, 8, norm, a.ksteps >= 8 ? 8 : 4};
+  } else if (epi == ROW_ROPE && a.K == f.d && a.N == (f.n_h + 2 * f.n_kv) * f.hd && f.hd % 64 == 0) {
+    const int cg = a.S >= 4 ? 1 : 4 / a.S;
+    s = {2, cg, std::max(8, a.S * cg), std::max(norm, (unsigned)(2 * a.S * cg) * 1024), a.ksteps >= 8 ? 8 : 4};
+  } else {
+    return false;
+  }
+  return a.N % (16 * s.ct * s.cg) == 0;
+}
+
+hipError_t launch_gemm_row(hipStream_t st, const GemmArgs& a, const RowArgs& f, int epi) {
+  if (a.ngroups < 1) return hipSuccess;
+  RowShape s;
+  if (!row_gemm_shape(a, f, epi, s)) return hipErrorInvalidValue;
   static bool attr = false;                // one attribute call per process for the kernels that hold rows in LDS
   if (!attr) {
     for (const void* k : {(const void*)k_gemm_row<2, 8, ROW_SWIGLU>, (const void*)k_gemm_row<2, 4, ROW_SWIGLU>,
@@ -2107,39 +2140,22 @@ hipError_t launch_gemm_row(hipStream_t st, const GemmArgs& a, const RowArgs& f, 
     }
     attr = true;
   }
-  // the rows and their sums (at most 129 KB), or after them the waves' partial sums
-  const unsigned norm = (unsigned)(rows * (f.d + kRowPad) + kRowMax * 16) * 4;
-  auto go = [&](auto kern, int ct, int cg, int waves, unsigned shm) {
-    const int cols = 16 * ct * cg;
-    if (a.N % cols != 0) return hipErrorInvalidValue;
-    const int ncb = a.N / cols, nblk = ncb * a.ngroups;
-    klaunch_shm(kern, dim3((nblk + 7) / 8 * 8), dim3(64 * waves), shm, st, a, f, ncb, cg);
+  const int ncb = a.N / (16 * s.ct * s.cg), nblk = ncb * a.ngroups;
+  auto go = [&](auto kern) {
+    klaunch_shm(kern, dim3((nblk + 7) / 8 * 8), dim3(64 * s.waves), s.lds, st, a, f, ncb, s.cg);
     return hipGetLastError();
   };
-  const bool deep = a.ksteps >= 8;                   // k-steps in flight: 8 or 4
-  if (epi == ROW_RES && a.N == f.d) {
-    // a column tile per workgroup; few splits are long chains in few waves, which
-    // keep 16 k-steps in flight
-    const unsigned sums = (unsigned)a.S * 1024;
-    if (a.S <= 4 && a.ksteps >= 16) return go(k_gemm_row<1, 16, ROW_RES>, 1, 1, a.S, sums);
-    if (deep) return go(k_gemm_row<1, 8, ROW_RES>, 1, 1, a.S, sums);
-    return go(k_gemm_row<1, 4, ROW_RES>, 1, 1, a.S, sums);
+  if (epi == ROW_RES) {
+    if (s.depth == 16) return go(k_gemm_row<1, 16, ROW_RES>);
+    if (s.depth == 8) return go(k_gemm_row<1, 8, ROW_RES>);
+    return go(k_gemm_row<1, 4, ROW_RES>);
   }
-  if (a.K != f.d) return hipErrorInvalidValue;
-  if (epi == ROW_SWIGLU && a.S == 1) {
-    // 128 columns per workgroup, 64 where that leaves CUs idle
-    const int cg = a.ngroups * (a.N / 128) >= 224 ? 4 : 2;
-    if (deep) return go(k_gemm_row<2, 8, ROW_SWIGLU>, 2, cg, 8, norm);
-    return go(k_gemm_row<2, 4, ROW_SWIGLU>, 2, cg, 8, norm);
+  if (epi == ROW_SWIGLU) {
+    if (s.depth == 8) return go(k_gemm_row<2, 8, ROW_SWIGLU>);
+    return go(k_gemm_row<2, 4, ROW_SWIGLU>);
   }
-  if (epi == ROW_ROPE && a.N == (f.n_h + 2 * f.n_kv) * f.hd && f.hd % 64 == 0) {
-    const int cg = a.S >= 4 ? 1 : 4 / a.S;
-    const int waves = std::max(8, a.S * cg);
-    const unsigned shm = std::max(norm, (unsigned)(2 * a.S * cg) * 1024);
-    if (deep) return go(k_gemm_row<2, 8, ROW_ROPE>, 2, cg, waves, shm);
-    return go(k_gemm_row<2, 4, ROW_ROPE>, 2, cg, waves, shm);
-  }
-  return hipErrorInvalidValue;
+  if (s.depth == 8) return go(k_gemm_row<2, 8, ROW_ROPE>);
+  return go(k_gemm_row<2, 4, ROW_ROPE>);
 }
 
 hipError_t launch_rope_kv(hipStream_t st, bool bf16, const float* part, int nsplit, size_t split_stride,

@@ -23,8 +23,9 @@
 //   * the row GEMMs' column groups, tiles and splits cover every column of a
 //     projection (for RoPE, both halves of every rotation pair in one wave) once,
 //     within the workgroup and the LDS that their launcher gives them.
-// The decode below restates the kernels' index arithmetic: a change to either
-// side that breaks the contract fails here, on the CPU. No HIP call is made.
+// The launchers' own acceptance rules are called; the decode below restates the
+// kernels' index arithmetic: a change to either side that breaks the contract
+// fails here, on the CPU. No HIP call is made.
 #include "../../paper_2606_03014_amd/csrc/engine.cpp"
 
 #include <cstdlib>
@@ -61,6 +62,8 @@ struct Tile { int kind; int rows; int cols; int S; };   // kind 0 f32, 1 small-M
 
 bool dispatchable(bool bf16, const GemmArgs& a, int epi, int mt, int nt, Tile& t, const char* what) {
   const int KS = a.K / 32;
+  CHECK(gemm_accepts(bf16, a, epi, mt, nt), "%s: the launcher refuses mt %d nt %d S %d ksteps %d epilogue %d", what, mt,
+        nt, a.S, a.ksteps, epi);
   if (!bf16) {
     CHECK(a.N % 64 == 0 && a.K % 64 == 0, "%s: f32 N %d K %d", what, a.N, a.K);
     CHECK(a.S == 1, "%s: f32 split %d", what, a.S);
@@ -122,22 +125,34 @@ bool f32_columns(const GemmArgs& a, int epi, const char* what) {
 // kRowSteps rows, and k_gemm_row's tile map.
 bool row_gemm(const moa_engine& e, const GemmPlanIn& in, int K, int N, int kind, const char* what) {
   const moa_model_cfg& m = e.cfg.model;
-  int maxM = 0, totalM = 0, groups = 0;
+  int maxM = 0, totalM = 0;
+  GemmArgs a{};
   for (int g = 0; g < in.ngroups; ++g) {
     maxM = std::max(maxM, in.nrows[g]);
     totalM += in.nrows[g];
-    groups += in.nrows[g] > 0;
+    if (in.nrows[g] > 0) a.g[a.ngroups++].nrows = in.nrows[g];
   }
   const int S = kind == ROW_SWIGLU ? 1 : small_split(&e, in, maxM, totalM, K, N), KS = K / 32;
   CHECK(S >= 1 && S <= 16 && KS % S == 0, "%s: row split %d of %d k-steps", what, S, KS);
   CHECK(kind == ROW_RES ? N == m.d_model : K == m.d_model, "%s: row K %d N %d", what, K, N);
-  const int ct = kind == ROW_RES ? 1 : 2;
-  const int cg = kind == ROW_RES ? 1 : (kind == ROW_SWIGLU ? (groups * (N / 128) >= 224 ? 4 : 2) : (S >= 4 ? 1 : 4 / S));
-  const int waves = kind == ROW_RES ? S : (kind == ROW_SWIGLU ? 8 : std::max(8, S * cg));
-  CHECK(waves <= 16 && S * cg <= waves, "%s: %d waves for %d splits of %d column groups", what, waves, S, cg);
-  CHECK(kind == ROW_RES || m.d_model <= waves * 64 * 4 * 2, "%s: d %d on %d waves", what, m.d_model, waves);
-  CHECK(kRowMax * (m.d_model + 4) * 4 + kRowMax * 64 <= 144 * 1024, "%s: LDS rows", what);
-  CHECK(N % (16 * ct * cg) == 0, "%s: row N %d in blocks of %d", what, N, 16 * ct * cg);
+  a.K = K;
+  a.N = N;
+  a.S = S;
+  a.ksteps = KS / S;
+  RowArgs f{};
+  f.d = m.d_model;
+  f.n_h = m.n_heads;
+  f.n_kv = m.n_kv_heads;
+  f.hd = m.head_dim;
+  RowShape rs;
+  CHECK(row_gemm_shape(a, f, kind, rs), "%s: the row launcher refuses it", what);
+  const int ct = rs.ct, cg = rs.cg;
+  CHECK(rs.waves <= 16 && S * cg <= rs.waves, "%s: %d waves for %d splits of %d column groups", what, rs.waves, S, cg);
+  CHECK(rs.depth <= 8 || rs.waves <= 4, "%s: depth %d on %d waves", what, rs.depth, rs.waves);
+  // a wave's partial sums; the rows, of which a thread normalises at most eight columns each
+  CHECK(rs.lds >= (kind == ROW_SWIGLU ? 0u : (unsigned)(S * cg * ct * 1024)) && rs.lds <= 144 * 1024, "%s: LDS %u", what, rs.lds);
+  CHECK(kind == ROW_RES || (m.d_model <= rs.waves * 64 * 4 * 2 && rs.lds >= (unsigned)(maxM * (m.d_model + 4) * 4 + kRowMax * 64)),
+        "%s: d %d on %d waves, LDS %u", what, m.d_model, rs.waves, rs.lds);
   std::vector<uint8_t> hit(N / 16, 0);
   for (int c = 0; c < N / (16 * ct); ++c)            // c = column block * cg + column group
     for (int j = 0; j < ct; ++j) {
