@@ -68,6 +68,29 @@ def test_step_noalloc_matches_step_twice_in_a_row(dtype):
             eng.close()
 
 
+def test_step_noalloc_uploads_admissions_that_its_staging_slot_cannot_hold():
+    """100 prompts of 2,700 tokens admitted in one step are more than the fixed 1 MiB staging slot of an
+    allocation-free step: they go up from host copies, one copy each, and the answers are moa_step's."""
+    import torch
+    assert torch.cuda.is_available()
+    shape = ModelShape(n_layers=1, d_model=256, n_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=128, vocab=512)
+    consts = EngineConsts(num_kv_blocks=100 * 170, max_num_seqs=100, max_prefill_tokens=4096, max_model_len=2710)
+    w = generate_weights(shape, "bf16", 5, 99, 0)
+    rng = np.random.default_rng(4)
+    reqs = [(rng.integers(0, shape.vocab, 2700), 0, 2) for _ in range(100)]
+    got = []
+    for noalloc in (False, True):
+        eng = Engine(shape, "bf16", consts, 1)
+        try:
+            mid = eng.load(pack_blob(w, shape))
+            got.append(_run(eng, [mid], reqs, shape.vocab, noalloc))
+        finally:
+            eng.close()
+    for i in range(100):
+        assert np.array_equal(got[0][0][i], got[1][0][i]), f"call {i}: tokens differ"
+        assert np.array_equal(got[0][1][i], got[1][1][i]) and np.all(np.isfinite(got[1][1][i])), f"call {i}"
+
+
 def test_step_noalloc_refuses_partials_beyond_the_scratch_on_a_gpu_engine():
     """An engine whose planned partials exceed the 64 MiB scratch gets
     MOA_ENOMEM and is left as it was: moa_step then runs its steps."""
