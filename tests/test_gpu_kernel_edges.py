@@ -93,10 +93,10 @@ def test_device_filled_histories_equal_uploaded_ones(dtype, hd, seats):
         assert np.array_equal(a, b)
 
 
-# small-M GEMM: 1, 8 (both planes packed in one MFMA), 9, 16, 17, 32 and 33 rows per model beside a smaller model; K of
-# 2 to 11 k-steps per wave (ffn 1408 splits neither way), a qkv width that is no multiple of 256 (384), and the
-# four-way split next to none
-@pytest.mark.parametrize("rows", [(1,), (8, 3), (9, 2), (16, 1), (17, 8), (32,), (33, 5), (64, 16), (65,)])
+# small-M GEMM: 1, 8, 9, 16, 17, 32 and 33 rows of a model beside another with fewer or more; splits of one to eleven
+# four-k-step stages (ffn 1408 has no split), a qkv width that is no multiple of 256 (384). The one-row batch alone has
+# its layers on the row GEMMs and only its head here
+@pytest.mark.parametrize("rows", [(1,), (1, 7), (8, 3), (9, 2), (16, 1), (17, 8), (32,), (33, 5), (64, 16), (65,)])
 @pytest.mark.parametrize("d,ffn,nh,nkv", [(256, 1408, 4, 1), (1024, 512, 2, 2), (512, 128, 8, 2)])
 def test_bf16_gemm_small_rows(rows, d, ffn, nh, nkv):
     shape = ModelShape(n_layers=1, d_model=d, n_heads=nh, n_kv_heads=nkv, head_dim=64, ffn_dim=ffn, vocab=1152)
@@ -112,8 +112,8 @@ def test_bf16_gemm_small_rows(rows, d, ffn, nh, nkv):
                     report_pure=False)
 
 
-# large-M GEMM: one chunk of 128 rows and a part, K of two k-steps (ffn 128 in 8 columns' worth), k-splits of uneven length,
-# 256- and 512-column tiles, a second model with a few rows in the same launches
+# large-M GEMM: chunks of 128 rows and a part, K of 4 k-steps (ffn 128, fewer than a split keeps), k-splits of uneven
+# length, 256- and 512-column tiles, a second model with a few rows in the same launches
 @pytest.mark.parametrize("rows", [(256,), (257, 3), (385,), (300, 290)])
 @pytest.mark.parametrize("d,ffn", [(256, 128), (1024, 768)])
 def test_bf16_gemm_large_rows(rows, d, ffn):
@@ -122,15 +122,20 @@ def test_bf16_gemm_large_rows(rows, d, ffn):
     _check(shape, "bf16", rows, 2, seed=sum(rows) + d, models=len(rows), consts=consts)
 
 
-# row GEMMs (steps of up to six rows over all models) and the step on either side of that: K of 4 k-steps (fewer than the
-# eight waves that share them), both head widths, one to eight query heads per KV head, prompts of one to three tokens
-# prefilled in such steps, one model and three on two streams
+# row GEMMs (steps of up to six rows over all models) and the step on either side of that: K of 4 k-steps (one split),
+# both head widths, one to eight query heads per KV head, prompts of one to three tokens prefilled in such steps, one
+# model and three on two streams. Every norm has gains of its own: another layer's, another model's or another column's
+# would show
 @pytest.mark.parametrize("rows", [(1,), (2, 3, 1), (6,), (7,), (4, 3)])
 @pytest.mark.parametrize("d,ffn,nh,nkv,hd", [(256, 128, 8, 1, 64), (512, 1408, 2, 2, 128), (2048, 256, 16, 8, 128)])
 def test_bf16_row_gemms(rows, d, ffn, nh, nkv, hd):
     shape = ModelShape(n_layers=2, d_model=d, n_heads=nh, n_kv_heads=nkv, head_dim=hd, ffn_dim=ffn, vocab=512)
     ws = [generate_weights(shape, "bf16", d + ffn, 97, m) for m in range(len(rows))]
     rng = np.random.default_rng(list(rows))
+    for w in ws:
+        for n in w:
+            if n.endswith("norm"):
+                w[n] = f32_to_bf16_bits(rng.uniform(0.25, 1.75, d).astype(np.float32))
     reqs = [(rng.integers(0, shape.vocab, 1 + (i + m) % 3).astype(np.int32), m, 4) for m, r in enumerate(rows)
             for i in range(r)]
     consts = EngineConsts(num_kv_blocks=64, max_num_seqs=8, max_prefill_tokens=6, max_model_len=64)
