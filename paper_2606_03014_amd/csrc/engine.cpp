@@ -24,6 +24,11 @@ namespace {
 constexpr int kStageSlots = 4;    // steps that may be in flight (pinned staging ring)
 constexpr int kBigMinRows = 256;    // a row group this large takes the large-M plan (128-row chunks)
 constexpr int kBigTargetWgs = 256;  // one workgroup per CU
+// Every model's weights start on this boundary of the arena, whatever lies before
+// them: us per step of three 1B models (four layers) at 24, 60 and 90 rows each 633,
+// 836, 816 where the sizes of the workspaces had put them 256 bytes past one and
+// 618, 813, 794 on it (also on 64 KB and 2 MB).
+constexpr size_t kModelAlign = 4096;
 // Large-M k-split cost, fitted to cold-weight sweeps of the 8B projections
 // (300 to 4,096 rows in one to four groups, S = 1..8; 4.6% rms): per
 // 32-wide k-step of a workgroup, each round of the grid over the CUs costs
@@ -176,7 +181,7 @@ Layout make_layout(const moa_engine_cfg& c) {
   L.block_bytes = (size_t)Lr * nkv * 2 * kBlock * hd * L.esz;
   L.kv_bytes = L.block_bytes * (size_t)c.num_kv_blocks;
   const size_t per_layer = (size_t)(2 * d + qkv * d + d * nh * hd + 3 * F * d) * L.esz;
-  L.model_bytes = align_up((size_t)(2 * V * d + d) * L.esz + 256 * (8 + 6 * Lr) + per_layer * Lr, 256);
+  L.model_bytes = align_up((size_t)(2 * V * d + d) * L.esz + 256 * (8 + 6 * Lr) + per_layer * Lr, kModelAlign);
 
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
@@ -202,8 +207,8 @@ Layout make_layout(const moa_engine_cfg& c) {
   L.off_xl = take((size_t)2 * L.Rmax * d * L.esz);
   L.off_pacc = take((size_t)L.slots_cap * nh * hd * 4);
   L.off_pml = take((size_t)L.slots_cap * nh * 2 * 4);
-  L.off_models = off;
-  L.total = off + L.model_bytes * (size_t)c.max_models;
+  L.off_models = align_up(off, kModelAlign);
+  L.total = L.off_models + L.model_bytes * (size_t)c.max_models;
   return L;
 }
 

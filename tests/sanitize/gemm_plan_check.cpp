@@ -19,6 +19,7 @@
 //   * gate-up (SwiGLU epilogue) is never split and, on the medium-M kernel,
 //     fits one workgroup per CU;
 //   * the large-M k-split still picks the splits measured best on the GPU;
+//   * every model's weights start on a 4 KB boundary of the arena;
 //   * a split projection whose k can be split has waves enough in flight;
 //   * the row GEMMs' column groups, tiles and splits cover every column of a
 //     projection (for RoPE, both halves of every rotation pair in one wave) once,
@@ -372,6 +373,10 @@ int main(int argc, char** argv) {
         e.cfg = cfg;
         e.bf16 = dt == 1;
         e.lay = make_layout(cfg);
+        if (e.lay.off_models % 4096 || e.lay.model_bytes % 4096) {
+          std::fprintf(stderr, "gemm_plan_check: models of %s at %zu, %zu bytes each\n", sh.name, e.lay.off_models, e.lay.model_bytes);
+          return 1;
+        }
         const moa_model_cfg& m = sh.m;
         const int qkv = (m.n_heads + 2 * m.n_kv_heads) * m.head_dim, qd = m.n_heads * m.head_dim;
         const Proj projs[5] = {
