@@ -539,7 +539,8 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
   //  * About one workgroup per CU. F32 projections take the k-split that
   //    brings this grid nearest ~224 workgroups; gate-up (no k-split: its
   //    SwiGLU epilogue needs the whole sum) takes the first tile shape whose
-  //    grid has 150..256 workgroups, else the small-M kernel.
+  //    grid has 150..256 workgroups, else the small-M kernel (but see below
+  //    for more than 64 rows).
   int sm_split = 0;                        // k-split of an F32 projection handed to the small-M kernel
   if (maxM > 16 && N % 256 == 0) {
     struct Shape { int rt, nw, ct; };
@@ -559,6 +560,14 @@ void plan_gemm(const moa_engine* e, const GemmPlanIn& in, int g0, int ng, int K,
         const int items = chunks_of(c.rt) * (N / (16 * c.nw * c.ct));
         if (items >= 150 && items <= 256) { sh = c; break; }
       }
+      // Past 64 rows a grid of more than 256 of the widest tiles stays on them: the
+      // small-M kernel would read the activations again for every 128 columns and
+      // every 64 rows (three 8B models of 150/150/60 rows, us per step of four layers
+      // 2,603 -> 2,101; four of 200/120/120/120 3,619 -> 2,831; ffn 13,952, two layers,
+      // 100/90/90 1,261 -> 1,021). Up to 64 rows that kernel is the faster one (five 8B
+      // models of 24 rows 2,012, 2,145 on the widest tiles).
+      const Shape widest = N % 512 == 0 ? cand[0] : cand[1];
+      if (!sh.rt && rt0 == 8 && chunks_of(8) * (N / (128 * widest.ct)) > 256) sh = widest;
     } else {
       sh = (rt0 >= 4 && N % 512 == 0) ? Shape{rt0, 8, 4} : (rt0 == 8 ? Shape{8, 8, 2} : Shape{rt0, 4, 4});
       if (allow_split) {

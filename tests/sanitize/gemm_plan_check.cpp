@@ -17,7 +17,7 @@
 //   * a share's launch picks the same tiling, split and partial stride as the
 //     whole step, so its partials land where the step's consumer reads them;
 //   * gate-up (SwiGLU epilogue) is never split and, on the medium-M kernel,
-//     fits one workgroup per CU;
+//     fits one workgroup per CU or takes the widest tiles;
 //   * the large-M k-split still picks the splits measured best on the GPU;
 //   * every model's weights start on a 4 KB boundary of the arena;
 //   * a split projection whose k can be split has waves enough in flight;
@@ -248,8 +248,20 @@ bool check_case(const moa_engine& e, const Proj& p, const GemmPlanIn& in, const 
   // launches are counted as large by the kernel that runs them
   CHECK(large == (e.bf16 && mt == kMmTile + 8 && nt > 24), "%s: large %d on mt %d nt %d", what, large, mt, nt);
   if (!p.split) CHECK(whole.S == 1, "%s: unsplit projection split %d ways", what, whole.S);
-  if (p.epi == EPI_SWIGLU && t.kind == 2 && !large)
-    CHECK(whole.total_items <= 256, "%s: gate-up medium grid %d", what, whole.total_items);
+  // medium-row gate-up: a grid that fits the CUs, or past 64 rows the widest tiles;
+  // there the small-M kernel only takes what would leave CUs idle
+  if (e.bf16 && p.epi == EPI_SWIGLU) {
+    int maxM = 0, chunks = 0;
+    for (int g = 0; g < in.ngroups; ++g) {
+      maxM = std::max(maxM, in.nrows[g]);
+      chunks += (in.nrows[g] + 127) / 128;
+    }
+    const int cols = p.N % 512 == 0 ? 512 : 256, widest = chunks * (p.N / cols);
+    if (t.kind == 2 && !large)
+      CHECK(whole.total_items <= 256 || (maxM > 64 && t.cols == cols), "%s: gate-up medium grid %d", what, whole.total_items);
+    if (t.kind == 1)
+      CHECK(maxM <= 64 || widest < 150, "%s: gate-up of %d rows in %d items on the small-M kernel", what, maxM, whole.total_items);
+  }
   // up to 64 rows a split projection is a stream of weights: 256 waves or more,
   // 32 columns each at most, unless k cannot be split so far (16 splits, 4 k-steps
   // each; the small-M kernel splits by twos in stages of 8 k-steps)

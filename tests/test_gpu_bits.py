@@ -76,6 +76,9 @@ BATCHES = {
     "rows 90 70 50": _rows((1, 1024, 8, 4, 64, 1792, 512), 90, 70, 50, G=3),
     "rows 130 20": _rows((1, 4096, 8, 2, 64, 1792, 512), 130, 20, G=2),
     "rows 200": _rows((1, 512, 8, 2, 64, 896, 512), 200, G=2),
+    # gate-up grids of more than 256 of the widest tiles, 512 and 256 columns
+    "rows 150 150 60": _rows((1, 256, 4, 2, 64, 16384, 512), 150, 150, 60, G=2),
+    "rows 100 100": _rows((1, 256, 4, 2, 64, 16512, 512), 100, 100, G=2),
 }
 
 
